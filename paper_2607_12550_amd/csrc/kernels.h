@@ -193,28 +193,37 @@ struct AttnBlob {
   const int8_t *gexp;          // per-slice core exponents
   const uint8_t *codes;        // packed residual codes (s, t, f) order, LSB first
   const uint16_t *scales;      // fp16 group scales
+  uint64_t seed;               // rotation signs
   int32_t rT, rd, bits, f16;
 };
 struct AttnItem {
   AttnBlob k, v;
   int32_t layer, pad;
 };
+// the items of a small call, passed to its first kernel by value (n = 0: they are in memory)
+constexpr int ATTN_TABLE_ITEMS = 16;
+struct AttnItemTable {
+  int32_t n, pad;
+  AttnItem it[ATTN_TABLE_ITEMS];
+};
 struct AttnArgs {
   const AttnItem *items;
-  const float *signs;          // [n_items][2][d]: key, value rotation signs
   const float *Q;              // [n_items][n_q][d]
   float *O;                    // [n_items][n_q][d]
   float *gk;                   // [n_items][n_q][rk_max]: 2^e G_s U_d^T q (key side)
   float *qr;                   // [n_items][n_q][d]: H (signs . q) / sqrt(d)
   float *part;                 // [n_items][chunks][n_q][2 + rv_max + d] chunk partials
   int32_t n_items, n_q, heads, T, group, chunks, rk_max, rv_max;
+  int32_t chunk_tokens, per_xcd, mfma;   // tokens per workgroup; the matrix-core pass and its grid
   float scale, inv_sqrt_d;
 };
-constexpr int ATTN_CHUNK = 64;      // tokens per workgroup of the chunk pass
+constexpr int ATTN_CHUNK = 64;      // tokens per workgroup of the vector chunk pass, per tile of the other
 constexpr int ATTN_QMAX = 64;       // query heads per item
 constexpr int ATTN_REP_MAX = 8;     // query heads per key-value head
 constexpr int ATTN_RT_MAX = 1024;   // largest value rank the combine kernel stages in LDS
-hipError_t launch_attend(const AttnArgs &a, int d, hipStream_t st);
+bool attend_use_mfma(const AttnItem *items, int n, int d, int group, int rep, int rk, int rv);
+int attend_chunk_tokens(int n_items, int heads, int T);
+hipError_t launch_attend(const AttnArgs &a, const AttnItemTable &tab, int d, hipStream_t st);
 // fixed per-device scratch of the allocation-free attention entry point
 constexpr size_t ATTN_SCRATCH_BYTES = JOLT_ATTEND_SCRATCH_BYTES;
 constexpr int ATTN_SCRATCH_DEVICES = 64;

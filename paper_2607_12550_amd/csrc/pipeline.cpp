@@ -1444,12 +1444,9 @@ extern "C" int jolt_slice_spectrum(jolt_ctx *ctx, const jolt_cell_desc *desc, in
 
 // ------------------------------------------------------------------------ attention on the factors
 namespace {
-void plan_attend(Carver &cv, int n, int n_q, int T, int d, int rk, int rv, AttnItem **items, uint64_t **seeds,
-                 float **signs, float **gk, float **qr, float **part) {
+void plan_attend(Carver &cv, int n, int n_q, int T, int d, int rk, int rv, AttnItem **items, float **gk, float **qr, float **part) {
   const int chunks = (T + ATTN_CHUNK - 1) / ATTN_CHUNK;
   *items = cv.take<AttnItem>(n);
-  *seeds = cv.take<uint64_t>(2 * (size_t)n);
-  *signs = cv.take<float>(2 * (size_t)n * d);
   *gk = cv.take<float>((size_t)n * n_q * std::max(rk, 1));
   *qr = cv.take<float>((size_t)n * n_q * d);
   *part = cv.take<float>((size_t)n * chunks * n_q * (2 + rv + d));
@@ -1462,8 +1459,8 @@ extern "C" int jolt_attend_workspace_size(int n_items, int n_q, int T, int d, in
       max_rT_v < 0 || max_rT_k > ATTN_RT_MAX || max_rT_v > ATTN_RT_MAX)
     return jolt_fail(JOLT_E_INVAL, "jolt_attend_workspace_size: bad argument (ranks <= %d)", ATTN_RT_MAX);
   Carver cv(nullptr);
-  AttnItem *it; uint64_t *sd; float *sg, *gk, *qr, *part;
-  plan_attend(cv, n_items, n_q, T, d, max_rT_k, max_rT_v, &it, &sd, &sg, &gk, &qr, &part);
+  AttnItem *it; float *gk, *qr, *part;
+  plan_attend(cv, n_items, n_q, T, d, max_rT_k, max_rT_v, &it, &gk, &qr, &part);
   *bytes = cv.off + 256;
   return JOLT_OK;
 }
@@ -1493,6 +1490,7 @@ int attend_impl(jolt_ctx *ctx, int n_items, const void *const *k_blobs, const si
       return jolt_fail(JOLT_E_BLOB, "item %d: key and value blobs differ in shape or group", i);
     if (a.T != z.T || a.d != z.d || a.heads != z.heads || a.group != z.group || a.m != z.m)
       return jolt_fail(JOLT_E_BLOB, "item %d: all items of a call must share m, T, d, heads and group", i);
+    if (a.rd > a.d || b.rd > b.d) return jolt_fail(JOLT_E_BLOB, "item %d: feature rank above d", i);
     if (!k_blobs[i] || !v_blobs[i]) return jolt_fail(JOLT_E_INVAL, "item %d: null blob", i);
     if (layers[i] < 0 || (int64_t)layers[i] * a.heads >= a.m)
       return jolt_fail(JOLT_E_INVAL, "item %d: layer %d outside the cell's %u layers", i, layers[i], a.m / a.heads);
@@ -1520,31 +1518,35 @@ int attend_impl(jolt_ctx *ctx, int n_items, const void *const *k_blobs, const si
   if (caller_ws) forget_spectra(ctx, ws, ws_bytes);
   hipStream_t st = (hipStream_t)stream;
   Carver cv(ws);
-  AttnItem *items; uint64_t *seeds; float *signs, *gk, *qr, *part;
-  plan_attend(cv, n_items, n_q, T, d, rk, rv, &items, &seeds, &signs, &gk, &qr, &part);
+  AttnItem *items; float *gk, *qr, *part;
+  plan_attend(cv, n_items, n_q, T, d, rk, rv, &items, &gk, &qr, &part);
   std::vector<AttnItem> hi(n_items);
-  std::vector<uint64_t> hs(2 * (size_t)n_items);
   auto blob = [](const void *base, const BlobInfo &b) {
     const uint8_t *p8 = static_cast<const uint8_t *>(base);
     return AttnBlob{p8 + b.L.UT, p8 + b.L.Ud, p8 + b.L.G, reinterpret_cast<const int8_t *>(p8 + b.L.gexp),
-                    p8 + b.L.codes, reinterpret_cast<const uint16_t *>(p8 + b.L.scales),
-                    (int32_t)b.rT, (int32_t)b.rd, (int32_t)b.bits, (int32_t)b.f16};
+                    p8 + b.L.codes, reinterpret_cast<const uint16_t *>(p8 + b.L.scales), b.seed,
+                    b.rd ? (int32_t)b.rT : 0, (int32_t)b.rd, (int32_t)b.bits, (int32_t)b.f16};
   };
-  for (int i = 0; i < n_items; ++i) {
-    hi[i] = AttnItem{blob(k_blobs[i], kb[i]), blob(v_blobs[i], vb[i]), layers[i], 0};
-    hs[2 * i] = kb[i].seed;
-    hs[2 * i + 1] = vb[i].seed;
+  for (int i = 0; i < n_items; ++i) hi[i] = AttnItem{blob(k_blobs[i], kb[i]), blob(v_blobs[i], vb[i]), layers[i], 0};
+  // up to 16 items travel as a kernel argument, more through one copy
+  AttnItemTable tab{};
+  if (n_items <= ATTN_TABLE_ITEMS) {
+    tab.n = n_items;
+    std::copy(hi.begin(), hi.end(), tab.it);
+  } else {
+    HIP_OK(hipMemcpyAsync(items, hi.data(), hi.size() * sizeof(AttnItem), hipMemcpyHostToDevice, st));
   }
-  HIP_OK(hipMemcpyAsync(items, hi.data(), hi.size() * sizeof(AttnItem), hipMemcpyHostToDevice, st));
-  HIP_OK(hipMemcpyAsync(seeds, hs.data(), hs.size() * sizeof(uint64_t), hipMemcpyHostToDevice, st));
-  HIP_OK(launch_rotation_signs(seeds, 2 * n_items, d, signs, st));
   AttnArgs a{};
-  a.items = items; a.signs = signs; a.Q = Q; a.O = O; a.gk = gk; a.qr = qr; a.part = part;
+  a.items = items; a.Q = Q; a.O = O; a.gk = gk; a.qr = qr; a.part = part;
   a.n_items = n_items; a.n_q = n_q; a.heads = H; a.T = T; a.group = kb[0].group;
-  a.chunks = (T + ATTN_CHUNK - 1) / ATTN_CHUNK; a.rk_max = std::max(rk, 1); a.rv_max = rv;
+  a.rk_max = std::max(rk, 1); a.rv_max = rv;
+  a.mfma = attend_use_mfma(hi.data(), n_items, d, a.group, n_q / H, a.rk_max, rv) ? 1 : 0;
+  a.chunk_tokens = a.mfma ? attend_chunk_tokens(n_items, H, T) : ATTN_CHUNK;
+  a.chunks = (T + a.chunk_tokens - 1) / a.chunk_tokens;
+  a.per_xcd = (int)(((int64_t)n_items * a.chunks * H + 7) / 8);
   a.scale = scale; a.inv_sqrt_d = (float)(1.0 / std::sqrt((double)d));
   StageTimer t(ctx, st, JOLT_STAGE_ATTEND);
-  HIP_OK(launch_attend(a, d, st));
+  HIP_OK(launch_attend(a, tab, d, st));
   return JOLT_OK;
 }
 }  // namespace
