@@ -26,6 +26,7 @@
 // WM x WN grid (2 x 2 for d >= 64), K = r_T in steps of 32 (zero-padded).  The 1-D grid
 // is remapped so that each XCD takes a contiguous run of tiles, ordered cell, slice, token
 // block: the token blocks of a slice share W_s, the slices of a cell share U^_T.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -967,6 +968,426 @@ __global__ void __launch_bounds__(NT, sizeof(TIO) == 2 ? 2 : 1) k_core(FusedArgs
   }
 }
 
+// ------------------------------------------------------- core path, factors resident in LDS
+// The same arithmetic as k_core, in the same order (the outputs are equal bit for bit), for bf16
+// caches of d >= 64 whose U^_d and G^_s^T fit the LDS together.  k_core waited most of its time:
+// one tile per workgroup, every operand chunk and every row staged through LDS between barriers.
+// Here a workgroup of eight waves keeps U^_d and G^_s^T of one slice in LDS and each wave walks
+// 32-token tiles of that slice on its own, with no barrier in the loop:
+//   * U^_T rows are loaded as stage 1's B operand straight into registers (lane = token);
+//   * codes and cache rows move as 16-byte pieces, lane (t, h) taking every second piece of row
+//     t, and v_permlane32_swap between the two lanes of a token brings them into (or from) the
+//     accumulator's feature order, so no staging is needed;
+//   * the next tile's U^_T rows are requested after stage 1, its codes after they are unpacked,
+//     its cache rows after they are subtracted.
+// RoPE: the frequencies as revolutions per token are formed once per workgroup in fp64, the
+// angle is reduced in revolutions in fp64, and cos and sin of the remaining |x| <= pi/4 are
+// Taylor polynomials in fp64 (truncation below 2^-36, under fp32's rounding).
+// 16 cells x 32 slices x 4096 tokens at ranks (128, 40), 8 bits: decode 717 us (k_core) -> 443 us,
+// 1.9 TB/s; with RoPE, 4 cells x 32 x 1777 at (96, 24), 4 bits: 156 -> 70 us.
+constexpr int CW_NT = 512;
+
+// LDS bytes for the largest U^_d and G^_s^T of a call
+JOLT_HD int core_w_lds(int D, int RD, int K16) { return D * (RD + 8) * 2 + RD * (K16 + 8) * 2 + 2 * (D / 8) * 8 + 64 * 8; }
+
+// the two registers' halves exchanged across the lane pair: a keeps its lower lanes and takes
+// b's lower lanes as its upper ones, b the upper lanes of both
+JOLT_DEV void pair_exchange(uint32_t &a, uint32_t &b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+
+// cos and sin of 2 pi x, x in revolutions (fp64), rounded to fp32
+JOLT_DEV void cos_sin_rev(double x, float &cs, float &sn) {
+  x -= __builtin_rint(x);
+  const double qd = __builtin_rint(4.0 * x);
+  const double y = fma(qd, -0.25, x) * 6.283185307179586476925;       // |y| <= pi / 4
+  const double z = y * y;
+  double s = fma(z, -1.0 / 39916800.0, 1.0 / 362880.0);
+  s = fma(z, s, -1.0 / 5040.0); s = fma(z, s, 1.0 / 120.0); s = fma(z, s, -1.0 / 6.0);
+  s = fma(z * s, y, y);
+  double c = fma(z, 1.0 / 479001600.0, -1.0 / 3628800.0);
+  c = fma(z, c, 1.0 / 40320.0); c = fma(z, c, -1.0 / 720.0); c = fma(z, c, 1.0 / 24.0);
+  c = fma(z, c, -0.5); c = fma(z, c, 1.0);
+  const int q = (int)qd & 3;
+  const float fc = (float)c, fs = (float)s;
+  const float a = (q & 1) ? fs : fc, b = (q & 1) ? fc : fs;
+  cs = (q == 1 || q == 2) ? -a : a;
+  sn = (q >= 2) ? -b : b;
+}
+
+template <int D, int MODE, bool ROPE>
+__global__ void __launch_bounds__(CW_NT, 1) k_core_w(FusedArgs a) {
+  constexpr int FB = D / 32, NU = D / 8, NV = D / 2, UB = 8;
+  extern __shared__ __attribute__((aligned(16))) uint8_t dyn[];
+  const int bi = blockIdx.x, jt = (bi & 7) * a.per_xcd + (bi >> 3);
+  if (jt >= a.total) return;
+  const int per_cell = a.m * a.tiles_t;
+  const int cell = jt / per_cell, rem = jt - cell * per_cell;
+  const int s = rem / a.tiles_t, part = rem - s * a.tiles_t;
+  const FusedCell c = a.cells[cell];
+  if (MODE == FUSED_RESIDUAL && c.bits == 0) return;
+  const int T = a.T, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tl = lane & 31, h = lane >> 5;
+  const int t_begin = part * a.wg_tokens, t_end = min(T, t_begin + a.wg_tokens);
+  const int64_t srow = (int64_t)(s / a.heads) * a.s_layer + (int64_t)(s % a.heads) * a.s_head;
+  const int bits = c.bits, g = a.group, gw = g / 8;
+  const int rT = c.rT, rd = c.rd;
+  const int ky = rT > 0 ? c.wexp[s] : 0;
+  const int xe = rT > 0 ? ky + (int)c.gexp[s] : 0;
+  const int RD = rT > 0 ? (rd + 31) & ~31 : 0, K16 = (rT + 15) & ~15, NB1 = RD / 32, NK = K16 / 16;
+  const int LDU = RD + 8, LDG = K16 + 8;
+  uint16_t *sud = reinterpret_cast<uint16_t *>(dyn), *sG = sud + D * LDU;
+  uint2 *smask = reinterpret_cast<uint2 *>(sG + RD * LDG);           // [h][u]: sign bits of 4 entries
+  double *rho = reinterpret_cast<double *>(smask + 2 * NU);          // revolutions per token
+  const float *sgn = a.signs + (int64_t)cell * D;
+
+  // ---- loads of one tile
+  const uint16_t *UT = reinterpret_cast<const uint16_t *>(c.UT);
+  const bool whole = (rT & 7) == 0;
+  ju4 ub[UB];
+  auto load_ub = [&](int t, int kk) -> ju4 {        // k chunk kk: entries 16 kk + 8 h ..
+    const int k = 16 * kk + 8 * h;
+    // entries past r_T meet zero columns of G^T; a row is read again from its last 8 entries
+    if (whole) return gload_u4(UT + (uint32_t)(t * rT + min(k, rT - 8)));
+    return load_run_h(UT, rT, t, T, k, rT);
+  };
+  auto load_ubs = [&](int t0) {
+    const int t = min(t0 + tl, T - 1);
+#pragma unroll
+    for (int q = 0; q < UB; ++q)
+      if (q < NK) ub[q] = load_ub(t, q);
+  };
+  constexpr int NIO = MODE == FUSED_RESIDUAL ? NU / 2 : NU / 4;
+  ju4 io[NIO];               // cache row: piece 2 k + h of 16 bytes; codes: piece 2 k + h
+  uint64_t scw = 0;
+  const int row_bytes = D * bits / 8, ng = D / g, lg = 31 - __builtin_clz(g);
+  const int nio = row_bytes / 32;                    // code pieces per lane (0: 16-byte rows)
+  auto load_io = [&](int t0) {
+    const int t = min(t0 + tl, T - 1);
+    if constexpr (MODE == FUSED_RESIDUAL) {
+      const uint8_t *x = reinterpret_cast<const uint8_t *>(c.x) + (srow + (int64_t)t * a.s_tok) * 2 + 16 * h;
+#pragma unroll
+      for (int k = 0; k < NIO; ++k) io[k] = gload_u4(x + 32 * k);
+    } else if (bits) {
+      const int64_t row = (int64_t)s * T + t;
+      const uint8_t *cb = c.codes + row * row_bytes + (nio ? 16 * h : 0);
+      io[0] = gload_u4(cb);
+#pragma unroll
+      for (int k = 1; k < NIO; ++k)
+        if (k < nio) io[k] = gload_u4(cb + 32 * k);
+      // the codes follow the scales, so 8 bytes are there from any row's first scale on
+      scw = *gptr(reinterpret_cast<const uint64_t *>(c.scales + row * ng));
+    }
+  };
+  const int tw = t_begin + 32 * wave;
+  if (tw < t_end) {
+    if (rT > 0) load_ubs(tw);
+    load_io(tw);
+  }
+
+  // ---- the slice's factors to LDS
+  if (rT > 0) {
+    for (int q = tid; q < D * RD / 8; q += CW_NT) {
+      const int f = q / (RD / 8), p8 = q - f * (RD / 8);
+      *reinterpret_cast<ju4 *>(sud + f * LDU + 8 * p8) = gload_u4(c.udp + (int64_t)f * RD + 8 * p8);
+    }
+    const uint16_t *Gt = reinterpret_cast<const uint16_t *>(c.Wt + (int64_t)s * D * c.ldw);
+    for (int q = tid; q < RD * K16 / 8; q += CW_NT) {
+      const int r = q / (K16 / 8), p8 = q - r * (K16 / 8);
+      *reinterpret_cast<ju4 *>(sG + r * LDG + 8 * p8) = gload_u4(Gt + (int64_t)r * K16 + 8 * p8);
+    }
+  }
+  if (tid < 2 * NU) {
+    const int f = 8 * (tid % NU) + 4 * (tid / NU);
+    uint32_t w[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      w[i] = (sgn[f + 2 * i] < 0.f ? 0x8000u : 0u) | (sgn[f + 2 * i + 1] < 0.f ? 0x80000000u : 0u);
+    // the residual keeps -s X
+    if (MODE == FUSED_RESIDUAL) { w[0] ^= 0x80008000u; w[1] ^= 0x80008000u; }
+    smask[tid] = make_uint2(w[0], w[1]);
+  }
+  if constexpr (ROPE)
+    if (tid < D / 2) rho[tid] = exp2(-(2.0 * tid / D) * a.rope_log2_base) * 0.159154943091895335769;
+  __syncthreads();
+
+  const uint2 *mask = smask + h * NU;
+  const int levels = (1 << bits) - 1;
+  const float mid = 0.5f * (float)levels;
+  const float psgn = h ? -1.f : 1.f;
+  for (int t0 = tw; t0 < t_end; t0 += 32 * (CW_NT / 64)) {
+    const int t = t0 + tl;
+    const bool tin = t < t_end, more = t0 + 32 * (CW_NT / 64) < t_end;
+    f32x16_t acc2[FB];
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc2[fb][q] = 0.f;
+    if constexpr (MODE == FUSED_DECODE) {
+      if (bits) {
+        float v[NV];
+        auto put = [&](int u, uint32_t cw) {
+          _Float16 dh;
+          const uint16_t db = (uint16_t)(scw >> (16 * ((8 * u) >> lg)));
+          __builtin_memcpy(&dh, &db, 2);
+          const float dl = (float)dh;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[4 * u + i] = ((float)((cw >> (bits * i)) & (uint32_t)levels) - mid) * dl;
+        };
+        if (bits == 8) {
+          // piece p of a row is units 2 p, 2 p + 1 of (lower, upper) lane words
+#pragma unroll
+          for (int k = 0; k < NU / 4; ++k)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              uint32_t x = io[k][2 * i], y = io[k][2 * i + 1];
+              pair_exchange(x, y);
+              put(4 * k + i, x);
+              put(4 * k + 2 + i, y);
+            }
+        } else if (bits == 4) {
+          // one word per unit, 16 bits per lane of the pair
+#pragma unroll
+          for (int k = 0; k < NU / 8; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              uint32_t x = io[k][i], y = x;
+              pair_exchange(x, y);
+              put(8 * k + i, (x >> (16 * h)) & 0xffffu);
+              put(8 * k + 4 + i, (y >> (16 * h)) & 0xffffu);
+            }
+        } else {
+          // one word per two units, 8 bits per lane of the pair (d = 64: one piece a row)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            uint32_t x = io[0][i], y = x;
+            if (D == 128) pair_exchange(x, y);
+            put(2 * i, (x >> (8 * h)) & 0xffu);
+            put(2 * i + 1, (x >> (16 + 8 * h)) & 0xffu);
+            if constexpr (D == 128) {
+              put(8 + 2 * i, (y >> (8 * h)) & 0xffu);
+              put(9 + 2 * i, (y >> (16 + 8 * h)) & 0xffu);
+            }
+          }
+        }
+        if (more) load_io(t0 + 32 * (CW_NT / 64));
+#pragma unroll
+        for (int w = 1; w < NV; w <<= 1)
+#pragma unroll
+          for (int k = 0; k < NV; ++k)
+            if ((k & w) == 0) {
+              const float p = v[k], q = v[k + w];
+              v[k] = p + q;
+              v[k + w] = p - q;
+            }
+#pragma unroll
+        for (int k = 0; k < NV; ++k) acc2[k >> 4][k & 15] = ldexpf(pair_butterfly(v[k], psgn) * a.inv_sqrt_d, -xe);
+      }
+    }
+    if (rT > 0) {
+      f32x16_t acc1[FB];
+#pragma unroll
+      for (int b = 0; b < FB; ++b)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc1[b][q] = 0.f;
+      for (int k0 = 0; k0 < NK; k0 += UB) {
+#pragma unroll
+        for (int q = 0; q < UB; ++q)
+          if (k0 + q < NK) {
+            const f16x8_t ubf = as_f16x8(ub[q]);
+#pragma unroll
+            for (int b = 0; b < FB; ++b)
+              if (b < NB1) {
+                const f16x8_t ga = *reinterpret_cast<const f16x8_t *>(sG + (32 * b + tl) * LDG + 16 * (k0 + q) + 8 * h);
+                acc1[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ga, ubf, acc1[b], 0, 0, 0);
+              }
+          }
+        if (k0 + UB < NK) {
+          const int tc = min(t, T - 1);
+#pragma unroll
+          for (int q = 0; q < UB; ++q)
+            if (k0 + UB + q < NK) ub[q] = load_ub(tc, k0 + UB + q);
+        }
+      }
+      if (more) load_ubs(t0 + 32 * (CW_NT / 64));
+#pragma unroll
+      for (int kc = 0; kc < 2 * FB; ++kc) {
+        if (kc < RD / 16) {
+          const int b = kc >> 1, cc = kc & 1;
+          f16x8_t yh, yl;
+#pragma unroll
+          for (int sl = 0; sl < 8; ++sl) {
+            const float yv = ldexpf(acc1[b][8 * cc + sl], -ky);
+            const _Float16 hi = (_Float16)yv;
+            yh[sl] = hi;
+            yl[sl] = (_Float16)(yv - (float)hi);
+          }
+#pragma unroll
+          for (int fb = 0; fb < FB; ++fb) {
+            const f16x8_t ua = *reinterpret_cast<const f16x8_t *>(sud + (32 * fb + tl) * LDU + 16 * kc + 8 * h);
+            acc2[fb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ua, yh, acc2[fb], 0, 0, 0);
+            acc2[fb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ua, yl, acc2[fb], 0, 0, 0);
+          }
+        }
+      }
+    }
+    float v[NV];
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) v[16 * fb + q] = ldexpf(acc2[fb][q], xe);     // exact
+
+    if constexpr (MODE == FUSED_RESIDUAL) {
+      // pieces 2 k (lower lane) and 2 k + 1 (upper): words (0, 1) are features 0 .. 3 of the
+      // unit, (2, 3) features 4 .. 7
+#pragma unroll
+      for (int k = 0; k < NU / 2; ++k) {
+        uint32_t w[4] = {io[k].x, io[k].y, io[k].z, io[k].w};
+        pair_exchange(w[0], w[2]);         // w[0]: unit 2 k, w[2]: unit 2 k + 1 (own features)
+        pair_exchange(w[1], w[3]);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int u = 2 * k + e;
+          const uint2 mk = mask[u];
+          const uint32_t x0 = w[2 * e] ^ mk.x, x1 = w[2 * e + 1] ^ mk.y;
+          v[4 * u] += __uint_as_float(x0 << 16);
+          v[4 * u + 1] += __uint_as_float(x0 & 0xffff0000u);
+          v[4 * u + 2] += __uint_as_float(x1 << 16);
+          v[4 * u + 3] += __uint_as_float(x1 & 0xffff0000u);
+        }
+      }
+      if (more) load_io(t0 + 32 * (CW_NT / 64));
+#pragma unroll
+      for (int w = 1; w < NV; w <<= 1)
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+          if ((k & w) == 0) {
+            const float p = v[k], q = v[k + w];
+            v[k] = p + q;
+            v[k + w] = p - q;
+          }
+#pragma unroll
+      for (int k = 0; k < NV; ++k) v[k] = pair_butterfly(v[k], psgn) * -a.inv_sqrt_d;
+      float am[NU];
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+        am[u] = fmaxf(fmaxf(fabsf(v[4 * u]), fabsf(v[4 * u + 1])), fmaxf(fabsf(v[4 * u + 2]), fabsf(v[4 * u + 3])));
+#pragma unroll
+      for (int w = 1; w < NU; w <<= 1)
+        if (w < gw) {
+#pragma unroll
+          for (int u = 0; u < NU; ++u)
+            if ((u & w) == 0) {
+              const float mm = fmaxf(am[u], am[u + w]);
+              am[u] = mm;
+              am[u + w] = mm;
+            }
+        }
+      const int64_t row = (int64_t)s * T + min(t, T - 1);
+      float delta = 0.f, inv = 0.f;
+      uint32_t cw[NU];
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        if ((u & (gw - 1)) == 0) {                            // first unit of a group
+          const float aa = pair_max(am[u]);
+          float dl = 2.f * aa / (float)levels;
+          dl = fminf(dl, 65504.f);
+          delta = f16_round(dl);
+          // r / delta as r * (1 / delta): within 1.5 ulp of the quotient
+          inv = delta == 0.f ? 0.f : 1.f / delta;
+          if (tin && h == 0) c.scales[row * ng + ((8 * u) >> lg)] = h_bits(delta);
+        }
+        uint32_t word = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float cq;
+          if (delta == 0.f) {
+            cq = (float)(1 << (bits - 1));
+          } else {
+            cq = __builtin_amdgcn_fmed3f(__builtin_rintf(fmaf(v[4 * u + i], inv, mid)), 0.f, (float)levels);
+          }
+          word |= (uint32_t)cq << (bits * i);
+        }
+        cw[u] = word;
+      }
+      uint8_t *cb = c.codes + row * row_bytes + (nio ? 16 * h : 0);
+      if (bits == 8) {
+#pragma unroll
+        for (int k = 0; k < NU / 4; ++k) {
+          pair_exchange(cw[4 * k], cw[4 * k + 2]);
+          pair_exchange(cw[4 * k + 1], cw[4 * k + 3]);
+          if (tin) *reinterpret_cast<JOLT_GLOBAL ju4 *>(gptr(cb + 32 * k)) = ju4{cw[4 * k], cw[4 * k + 2], cw[4 * k + 1], cw[4 * k + 3]};
+        }
+      } else if (bits == 4) {
+#pragma unroll
+        for (int k = 0; k < NU / 8; ++k) {
+          ju4 o;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            // units 8 k + i (stored by the lower lane) and 8 k + 4 + i (by the upper)
+            uint32_t x = cw[8 * k + i], y = cw[8 * k + 4 + i];
+            pair_exchange(x, y);           // own unit's lower-lane and upper-lane halves
+            o[i] = x | (y << 16);
+          }
+          if (tin) *reinterpret_cast<JOLT_GLOBAL ju4 *>(gptr(cb + 32 * k)) = o;
+        }
+      } else {
+        ju4 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if constexpr (D == 128) {
+            uint32_t x = cw[2 * i] | (cw[2 * i + 1] << 16), y = cw[8 + 2 * i] | (cw[9 + 2 * i] << 16);
+            pair_exchange(x, y);
+            o[i] = x | (y << 8);
+          } else {
+            uint32_t x = cw[2 * i] | (cw[2 * i + 1] << 16), y = x;
+            pair_exchange(x, y);
+            o[i] = x | (y << 8);
+          }
+        }
+        if (tin && (D == 128 || h == 0)) *reinterpret_cast<JOLT_GLOBAL ju4 *>(gptr(cb)) = o;
+      }
+    } else {
+      if constexpr (ROPE) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+          const uint2 mk = mask[u];
+          v[4 * u] = __uint_as_float(__float_as_uint(v[4 * u]) ^ (mk.x << 16));
+          v[4 * u + 1] = __uint_as_float(__float_as_uint(v[4 * u + 1]) ^ (mk.x & 0x80000000u));
+          v[4 * u + 2] = __uint_as_float(__float_as_uint(v[4 * u + 2]) ^ (mk.y << 16));
+          v[4 * u + 3] = __uint_as_float(__float_as_uint(v[4 * u + 3]) ^ (mk.y & 0x80000000u));
+        }
+        const double pos = (double)(t + a.rope_offset);
+#pragma unroll
+        for (int k = 0; k < NV / 2; ++k) {
+          float cf, sf;
+          if (k % 2 == 0) __builtin_amdgcn_sched_barrier(0);     // bounds the live fp64 values
+          cos_sin_rev(pos * rho[8 * (k / 4) + 4 * h + (k % 4)], cf, sf);
+          const float lo = v[k], hi = v[k + NV / 2];
+          v[k] = fmaf(-hi, sf, lo * cf);
+          v[k + NV / 2] = fmaf(lo, sf, hi * cf);
+        }
+      }
+      uint8_t *ob = reinterpret_cast<uint8_t *>(c.out) + (srow + (int64_t)min(t, T - 1) * a.s_tok) * 2 + 16 * h;
+#pragma unroll
+      for (int k = 0; k < NU / 2; ++k) {
+        uint32_t w[4];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int u = 2 * k + e;
+          w[2 * e] = (uint32_t)f32_to_bf16(v[4 * u]) | ((uint32_t)f32_to_bf16(v[4 * u + 1]) << 16);
+          w[2 * e + 1] = (uint32_t)f32_to_bf16(v[4 * u + 2]) | ((uint32_t)f32_to_bf16(v[4 * u + 3]) << 16);
+          if constexpr (!ROPE) { const uint2 mk = mask[u]; w[2 * e] ^= mk.x; w[2 * e + 1] ^= mk.y; }
+        }
+        pair_exchange(w[0], w[2]);         // unit 2 k to the lower lane, 2 k + 1 to the upper
+        pair_exchange(w[1], w[3]);
+        if (tin) *reinterpret_cast<JOLT_GLOBAL ju4 *>(gptr(ob + 32 * k)) = ju4{w[0], w[1], w[2], w[3]};
+      }
+    }
+  }
+}
+
 template <int D, int MODE, typename TIO, bool USPLIT>
 hipError_t launch_mode(const FusedArgs &a, bool rope, hipStream_t st) {
   const dim3 grid((unsigned)(a.per_xcd * 8)), block(NT);
@@ -1003,9 +1424,43 @@ hipError_t launch_core(const FusedArgs &a, int io_dtype, bool rope, hipStream_t 
   return hipGetLastError();
 }
 
+// The resident-factor kernel's calls: bf16 caches, a code row of whole 16-byte pieces (d >= 64),
+// at most four group scales a row (one 8-byte read), factors within the LDS.
+template <int D, int MODE>
+bool core_w_takes(const FusedArgs &a, int io_dtype) {
+  if (D < 64 || MODE == FUSED_XTILDE || io_dtype != JOLT_BF16 || a.group * 4 < D) return false;
+  return core_w_lds(D, (a.rd_max + 31) & ~31, (a.rT_max + 15) & ~15) <= 160 * 1024 - 512;
+}
+
+// A workgroup walks as many 256-token rounds of its slice as leave about 512 workgroups, two
+// rounds of the chip (its prologue reads the slice's factors).
+template <int D, int MODE>
+hipError_t launch_core_w(FusedArgs a, bool rope, hipStream_t st) {
+  const int64_t slices = (int64_t)a.n_cells * a.m, rounds = (a.T + 255) / 256;
+  a.wg_tokens = 256 * (int32_t)std::min<int64_t>(rounds, std::max<int64_t>(1, slices * rounds / 512));
+  a.tiles_t = (a.T + a.wg_tokens - 1) / a.wg_tokens;
+  a.total = (int32_t)(slices * a.tiles_t);
+  a.per_xcd = (a.total + 7) / 8;
+  const int lds = core_w_lds(D, (a.rd_max + 31) & ~31, (a.rT_max + 15) & ~15);
+  auto go = [&](auto kernel) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(a.per_xcd * 8)), dim3(CW_NT), lds, st, a);
+    return hipGetLastError();
+  };
+  if constexpr (MODE == FUSED_DECODE)
+    if (rope) return go(&k_core_w<D, MODE, true>);
+  return go(&k_core_w<D, MODE, false>);
+}
+
 template <int MODE>
 hipError_t launch_m(const FusedArgs &a, int d, int io_dtype, bool split, bool rope, hipStream_t st) {
   if (!split) {
+    if constexpr (MODE != FUSED_XTILDE) {
+      if (d == 64 && core_w_takes<64, MODE>(a, io_dtype)) return launch_core_w<64, MODE>(a, rope, st);
+      if (d == 128 && core_w_takes<128, MODE>(a, io_dtype)) return launch_core_w<128, MODE>(a, rope, st);
+    }
     switch (d) {
       case 32: return launch_core<32, MODE>(a, io_dtype, rope, st);
       case 64: return launch_core<64, MODE>(a, io_dtype, rope, st);

@@ -44,7 +44,8 @@ struct FusedArgs {
   const FusedCell *cells;   // device [n_cells]
   const float *signs;       // device [n_cells][d]
   int32_t n_cells, m, T, heads, group;
-  int32_t tiles_t, total, per_xcd;    // set by launch_fused
+  int32_t tiles_t, total, per_xcd, wg_tokens;    // set by launch_fused
+  int32_t rT_max, rd_max;             // largest ranks of the call's cells
   int64_t s_layer, s_head, s_tok;     // cell strides (input for the residual, output for decode)
   float inv_sqrt_d;
   int32_t rope, rope_offset, pad;

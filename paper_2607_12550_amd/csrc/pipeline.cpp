@@ -527,8 +527,10 @@ FusedCell fused_cell(Run &R, int c, int m, int d, const BlobView &v) {
   return f;
 }
 
-FusedArgs fused_args(Run &R, int nc, int m, int T, int d, int group, const jolt_cell_desc *strides) {
+FusedArgs fused_args(Run &R, int nc, int m, int T, int d, int group, const jolt_cell_desc *strides,
+                     const std::vector<FusedCell> &fc) {
   FusedArgs a{};
+  for (const FusedCell &c : fc) { a.rT_max = std::max(a.rT_max, c.rT); a.rd_max = std::max(a.rd_max, c.rd); }
   a.cells = R.w.fcell_r; a.signs = R.w.signs;
   a.n_cells = nc; a.m = m; a.T = T; a.heads = strides->n_heads; a.group = group;
   a.s_layer = strides->stride_layer; a.s_head = strides->stride_head; a.s_tok = strides->stride_token;
@@ -1047,7 +1049,7 @@ extern "C" int jolt_compress(jolt_ctx *ctx, const jolt_cell_desc *desc, int n_ce
   }
   if (any_bits) {
     StageTimer t(R.ctx, R.st, JOLT_STAGE_RESIDUAL);
-    HIP_OK(launch_fused(fused_args(R, nc, m, T, d, params[0].group, desc), FUSED_RESIDUAL, d, desc->dtype,
+    HIP_OK(launch_fused(fused_args(R, nc, m, T, d, params[0].group, desc, fc), FUSED_RESIDUAL, d, desc->dtype,
                         !f16, R.st));
   }
   // headers
@@ -1075,7 +1077,7 @@ extern "C" int jolt_compress(jolt_ctx *ctx, const jolt_cell_desc *desc, int n_ce
   // the X~ export re-runs the fused pass in its export mode on this call's W_s^T
   dbg.fused = fc;
   dbg.fcell_dev = R.w.fcell_r;
-  dbg.fargs = fused_args(R, nc, m, T, d, params[0].group, desc);
+  dbg.fargs = fused_args(R, nc, m, T, d, params[0].group, desc, fc);
   dbg.split = !f16;
   dbg.Omega = R.w.Om; dbg.om_stride = (int64_t)N * R.w.ldo; dbg.ldo = R.w.ldo;
   return JOLT_OK;
@@ -1318,7 +1320,7 @@ extern "C" int jolt_decompress_rope(jolt_ctx *ctx, int n_cells, const void *cons
   } else {
     HIP_OK(hipMemcpyAsync(R.w.fcell_r, fc.data(), n_cells * sizeof(FusedCell), hipMemcpyHostToDevice, st));
   }
-  FusedArgs a = fused_args(R, n_cells, m, T, d, bi[0].group, out);
+  FusedArgs a = fused_args(R, n_cells, m, T, d, bi[0].group, out, fc);
   if (rope) {
     a.rope = 1;
     a.rope_offset = rope->position_offset;
