@@ -245,7 +245,11 @@ struct EigBatch {
 };
 inline __host__ __device__ int refl_off(const EigBatch &b) { return b.refl_off > 0 ? b.refl_off : 1; }
 // Householder tridiagonalisation (lower): small n in one workgroup per matrix.
-hipError_t launch_sytrd_small(const EigBatch &b, hipStream_t st);
+// register-resident tridiagonalisation (n <= TRD_REG_MAX); spin_max bounds its waits, a matrix
+// that gave up has e[n-1] = NaN (0 otherwise)
+constexpr int TRD_REG_MAX = 1024;
+int trd_reg_workgroups(int n);       // workgroups per matrix
+hipError_t launch_trd_reg(const EigBatch &b, int spin_max, hipStream_t st);
 // Blocked multi-workgroup tridiagonalisation for large n (panels of nb columns).
 // work: sytrd_large_work_floats() device floats; tables: sytrd_large_table_entries().
 struct SytrdArgs {

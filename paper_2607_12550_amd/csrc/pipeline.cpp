@@ -237,10 +237,17 @@ struct Run {
   }
 };
 
+// Matrices up to order 768 are tridiagonalised in registers, larger ones too unless a
+// reduction was asked for by name, as long as the whole batch fits the chip at once.
+bool trd_in_registers(const jolt_ctx *c, const EigBatch &b) {
+  if (b.n <= SYTRD_SMALL_MAX) return true;
+  return c->trd_two_stage < 0 && b.n <= TRD_REG_MAX && (int64_t)b.n_mat * trd_reg_workgroups(b.n) <= 256;
+}
+
 // symmetric eigenvalues (all) of the n x n matrices in e.b.A
 int eig_values(Run &R, EigWs &e) {
-  if (e.b.n > SYTRD_SMALL_MAX) {
-    jolt_ctx *c = R.ctx;
+  jolt_ctx *c = R.ctx;
+  if (!trd_in_registers(c, e.b)) {
     // Two stages (band of half-bandwidth sb_band(), then bulge chasing) move the trailing
     // matrix once per panel instead of once per column, but their bulge chase is a chain of
     // about n^2 / 64 dependent steps per matrix; the one-stage reduction costs about n^3 / 6
@@ -306,8 +313,9 @@ int eig_values(Run &R, EigWs &e) {
       for (int g = 1; g < lanes; ++g) HIP_OK(hipStreamWaitEvent(R.st, c->trd_join[g], 0));
     }
   } else {
+    e.b.refl_off = 1;
     StageTimer t(R.ctx, R.st, JOLT_STAGE_TRIDIAG_SMALL);
-    HIP_OK(launch_sytrd_small(e.b, R.st));
+    HIP_OK(launch_trd_reg(e.b, c->bulge_spin, R.st));
   }
   StageTimer t(R.ctx, R.st, JOLT_STAGE_EIGVALS);
   HIP_OK(launch_tridiag_eigvals(e.b, R.st));
@@ -334,7 +342,7 @@ int eig_vectors(Run &R, EigWs &e, const std::vector<int> &k, float *U, int64_t l
   R.ctx->tab_host.resize(std::max(R.ctx->tab_host.size(), nt));
   // two-stage reduction: the band-to-tridiagonal reflectors first (Z -> U), then the
   // panel reflectors of the first stage by the blocked back-transform
-  const bool two = e.b.n > SYTRD_SMALL_MAX && e.b.refl_off == sb_band();
+  const bool two = e.b.refl_off == sb_band();
   if (two) HIP_OK(launch_sb_q2(e.b, e.trd, iw, kmax, U, ldu, u_stride, R.st));
   HIP_OK(launch_backtransform(e.b, iw, kmax, k.data(), U, ldu, u_stride, e.bt, tab, R.ctx->tab_host.data(), R.st,
                               two));
@@ -361,10 +369,15 @@ struct CallChecks {
       n_orth = R.orth_calls;
       // a bulge chase that gave up leaves NaN on its diagonal
       const EigBatch &tb = R.w.teig.b;
-      if (tb.d && tb.n > SYTRD_SMALL_MAX && tb.refl_off == sb_band()) {
+      if (tb.d && tb.refl_off == sb_band()) {
         d0.resize(tb.n_mat);
         HIP_OK(hipMemcpy2DAsync(d0.data(), sizeof(double), tb.d, (size_t)tb.n * sizeof(double), sizeof(double),
                                 tb.n_mat, hipMemcpyDeviceToHost, R.st));
+      } else if (tb.d && trd_reg_workgroups(tb.n) > 1) {
+        // and a register-resident reduction that gave up NaN as its (unused) last off-diagonal
+        d0.resize(tb.n_mat);
+        HIP_OK(hipMemcpy2DAsync(d0.data(), sizeof(double), tb.e + tb.n - 1, (size_t)tb.n * sizeof(double),
+                                sizeof(double), tb.n_mat, hipMemcpyDeviceToHost, R.st));
       }
       if (n_orth) {
         clamp.resize((size_t)n_orth * 2 * nc);
@@ -399,7 +412,7 @@ struct CallChecks {
     }
     for (int c = 0; c < (int)d0.size(); ++c)
       if (!std::isfinite(d0[c]))
-        return jolt_fail(JOLT_E_NOCONV, "cell %d: the band-to-tridiagonal reduction of the token Gram did not complete", c);
+        return jolt_fail(JOLT_E_NOCONV, "cell %d: the tridiagonal reduction of the token Gram did not complete", c);
     for (int c = 0; c < (int)tstat.size(); ++c)
       if (tstat[c]) return jolt_fail(JOLT_E_NOCONV, "cell %d: token-mode inverse iteration did not converge", c);
     for (int c = 0; c < (int)fstat.size(); ++c)
@@ -1430,15 +1443,20 @@ extern "C" int jolt_slice_spectrum(jolt_ctx *ctx, const jolt_cell_desc *desc, in
   }
   {
     StageTimer t(ctx, st, JOLT_STAGE_TRIDIAG_SMALL);
-    HIP_OK(launch_sytrd_small(e.b, st));
+    HIP_OK(launch_trd_reg(e.b, ctx->bulge_spin, st));
   }
   {
     StageTimer t(ctx, st, JOLT_STAGE_EIGVALS);
     HIP_OK(launch_tridiag_eigvals(e.b, st));
   }
-  std::vector<double> lam((size_t)n_cells * m);
+  std::vector<double> lam((size_t)n_cells * m), last(n_cells);
+  HIP_OK(hipMemcpy2DAsync(last.data(), sizeof(double), e.b.e + m - 1, (size_t)m * sizeof(double), sizeof(double),
+                          n_cells, hipMemcpyDeviceToHost, st));
   HIP_OK(hipMemcpyAsync(lam.data(), e.b.lam, lam.size() * sizeof(double), hipMemcpyDeviceToHost, st));
   HIP_OK(hipStreamSynchronize(st));
+  for (int c = 0; c < n_cells; ++c)
+    if (!std::isfinite(last[c]))
+      return jolt_fail(JOLT_E_NOCONV, "cell %d: the tridiagonal reduction of the slice Gram did not complete", c);
   // eigenvalues are clipped at 0 (the Gram is positive semi-definite)
   for (size_t i = 0; i < lam.size(); ++i) lam_s[i] = std::max(0.0, lam[i]);
   return JOLT_OK;
