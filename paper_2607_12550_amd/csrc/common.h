@@ -101,6 +101,13 @@ JOLT_DEV float wave_sum(float v) {
   return v;
 }
 
+// 1/x: the hardware estimate and two Newton steps
+JOLT_DEV double recip2(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
+
 // ---------------------------------------------------------------- cell addressing
 // Element (s, t, f) of a cell: base + (s / heads) * s_layer + (s % heads) * s_head + t * s_tok + f
 struct CellView {

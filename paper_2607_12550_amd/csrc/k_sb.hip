@@ -17,8 +17,8 @@
 // band.  Each step touches three SB x SB blocks (the previous bulge block, the diagonal
 // block and the block below) of a band buffer holding 2 SB entries per column; sweep s + 1
 // may run step k once sweep s has completed step k + 2 (k + 3 here, so that the next step's
-// blocks can be loaded during the current one).  One workgroup per matrix, one wavefront per
-// sweep in flight, the dependencies between wavefronts kept in LDS.
+// blocks can be loaded during the current one).  One wavefront per sweep in flight, the wavefronts
+// of a matrix spread over several workgroups, progress words in memory between them.
 //
 // Eigenvectors: z of the tridiagonal -> Q2 z (the stage-2 reflectors in blocks of 32 sweeps
 // at one step, groups of sweeps last to first, steps in increasing order within a group) ->
@@ -40,7 +40,8 @@ constexpr int SBW = 2 * SB;       // band-buffer entries per column (band and bu
 constexpr int PQ_NT = 1024;       // panel QR: threads per matrix
 constexpr int SY_ROWS = 128;      // rows of X per workgroup of the symmetric product
 constexpr int SY_NT = 256;
-constexpr int BG_WAVES = 8;       // bulge chase: wavefronts (sweeps in flight) per matrix
+constexpr int BG_WAVES = 4;       // bulge chase: wavefronts per workgroup, one per SIMD
+constexpr int BG_DONE = 1 << 20;  // progress word of a finished sweep (above any step count)
 constexpr int BT_BLOCK = 128;     // reflectors per block of the stage-1 back-transform
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
@@ -84,9 +85,9 @@ JOLT_DEV SbView sview(const SbArgs &a, int mat) {
 JOLT_DEV void house(float alpha, float sigma, float &tau, float &beta, float &scal) {
   if (sigma == 0.f) { tau = 0.f; beta = alpha; scal = 0.f; return; }
   const double b = -copysign(sqrt((double)alpha * alpha + (double)sigma), (double)alpha);
-  tau = (float)((b - alpha) / b);
+  tau = (float)((b - alpha) * recip2(b));
   beta = (float)b;
-  scal = (float)(1.0 / (alpha - b));
+  scal = (float)recip2(alpha - b);
 }
 
 // base[idx] with a uniform base and a 32-bit element index: the access takes the
@@ -504,18 +505,46 @@ __global__ void __launch_bounds__(SY_NT) k_sb_zform(SbArgs a, int p, int mat0) {
 // Lane (j, h) of a wavefront holds rows 16 h .. 16 h + 15 of column j of L and D, and
 // columns 16 h .. 16 h + 15 of row j of E; v, w and E's transpose go through LDS.
 // Reflector (s, k) is stored as [tau, v_1 .. v_31] (v_0 = 1) for the back-transform.
-__global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0) {
-  const int mat = mat0 + blockIdx.x, n = a.n;
+//
+// A sweep is a chain of n / 32 steps and may follow the one before at a distance of four, so
+// about n / 150 sweeps can be in flight; eight wavefronts in one workgroup per matrix left 240
+// CUs idle and ran two waves per SIMD (157 ms at n = 4096, for 4 or 16 matrices alike).  Here
+// the sweeps of a matrix are spread over the wavefronts of several workgroups: a wavefront
+// draws its next sweep from the matrix's ticket, in order, so that a drawn sweep's
+// predecessor is always finished or running whichever workgroups are on the chip.  Band entries
+// and progress words are relaxed agent-scope atomics (coherent across the XCDs); a step's stores
+// have completed (vmcnt) before its progress word is written, at the start of the next step, when
+// the wave has waited for its loads anyway.  Eight matrices of order 4096 per launch: 157 ms with
+// one workgroup each -> 86 ms with eight.
+JOLT_DEV float band_ld(const float *base, uint32_t idx) {
+  return __uint_as_float(__hip_atomic_load(reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(base) + 4u * idx),
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+JOLT_DEV void band_st(float *base, uint32_t idx, float v) {
+  __hip_atomic_store(reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(base) + 4u * idx), __float_as_uint(v),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+JOLT_DEV int word_ld(const int *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+JOLT_DEV void word_st(int *p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// per matrix, in stage 1's X area (n x SB floats): ticket, abort word, then (from word 64 on) one
+// progress word per sweep
+JOLT_DEV int *bulge_words(const SbView &M) { return reinterpret_cast<int *>(M.X); }
+
+__global__ void __launch_bounds__(256) k_sb_bulge_clear(SbArgs a, int mat0) {
+  int *w = bulge_words(sview(a, mat0 + blockIdx.x));
+  for (int i = threadIdx.x; i < a.n + 64; i += 256) word_st(w + i, 0);
+}
+
+__global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0, int groups) {
+  const int mat = mat0 + blockIdx.x / groups, n = a.n;
   const SbView M = sview(a, mat);
   const int km = steps_max(n);
   __shared__ float tb[BG_WAVES][SB][SB + 1];
   __shared__ float vb[BG_WAVES][SB], wb[BG_WAVES][SB];
-  __shared__ int prog[BG_WAVES];
-  __shared__ int abort_flag;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, lj = lane & 31, h = lane >> 5;
-  if (tid < BG_WAVES) prog[tid] = -1;
-  if (tid == 0) abort_flag = 0;
-  __syncthreads();
+  const int tid = threadIdx.x, lane = tid & 63, lj = lane & 31, h = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int *words = bulge_words(M), *prog = words + 64;
   float *AB = M.AB;
   const int nsw = n - 2;
   // block loads of step k of a sweep: E (row layout) and D (diagonal-offset layout: lane lj
@@ -526,49 +555,58 @@ __global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0) 
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const int c = 16 * h + q;
-      E[q] = (lj < ne && c < ln) ? ldx(AB, (uint32_t)((r0 + c) * SBW + (ln + lj - c))) : 0.f;
-      D[q] = (c + lj < ln) ? ldx(AB, (uint32_t)((r0 + c) * SBW + lj)) : 0.f;
+      E[q] = (lj < ne && c < ln) ? band_ld(AB, (uint32_t)((r0 + c) * SBW + (ln + lj - c))) : 0.f;
+      D[q] = (c + lj < ln) ? band_ld(AB, (uint32_t)((r0 + c) * SBW + lj)) : 0.f;
     }
   };
-  for (int s = wv; s < nsw; s += BG_WAVES) {
+  while (true) {
+    int s = 0;
+    if (lane == 0) s = __hip_atomic_fetch_add(words, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s = __builtin_amdgcn_readfirstlane(s);
+    if (s >= nsw) break;
     float L[16], D[16], E[16], Dn[16], En[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) { L[q] = 0.f; Dn[q] = 0.f; En[q] = 0.f; }
     int r0 = s + 1;
     bool stop = false;
+    int seen = s > 0 ? 0 : BG_DONE;      // progress of sweep s - 1 as last read
     for (int k = 0;; ++k) {
       const int r1 = min(r0 + SB, n), ln = r1 - r0;
       if (ln < 2) break;
+      if (k > 0) {
+        // the previous step's stores (and the loads for this step) have completed
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0) word_st(prog + s, k);
+      }
       // Step k + 1's blocks are loaded during step k, so sweep s - 1 must have completed
       // step k + 3 (step k itself needs k + 2).
-      if (s > 0) {
-        const int need = (s - 1) * 1024 + k + 4;
-        int spins = 0;
+      if (seen < k + 4) {
         if (a.spin_max == 0) stop = true;
+        int spins = 0;
         while (!stop) {
-          const int v = __hip_atomic_load(&prog[(s - 1) % BG_WAVES], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-          if (v >= need) break;
-          if (++spins > a.spin_max || __hip_atomic_load(&abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
-            stop = true;
-            break;
-          }
-          __builtin_amdgcn_s_sleep(1);
+          seen = __builtin_amdgcn_readfirstlane(word_ld(prog + s - 1));
+          if (seen >= k + 4) break;
+          if (++spins > a.spin_max || ((spins & 63) == 0 && word_ld(words + 1) != 0)) stop = true;
+          else __builtin_amdgcn_s_sleep(1);
         }
         if (stop) break;
       }
+      asm volatile("" ::: "memory");
       const int r2 = min(r1 + SB, n), ne = r2 - r1;
       if (k == 0) {
         load_blocks(r0, D, E);
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
           const int i = 16 * h + q;
-          L[q] = (lj == 0 && i < ln) ? ldx(AB, (uint32_t)(s * SBW + 1 + i)) : 0.f;
+          L[q] = (lj == 0 && i < ln) ? band_ld(AB, (uint32_t)(s * SBW + 1 + i)) : 0.f;
         }
       } else {
 #pragma unroll
         for (int q = 0; q < 16; ++q) { D[q] = Dn[q]; E[q] = En[q]; }
       }
       if (ne >= 2) load_blocks(r1, Dn, En);
+      // sweep s - 1's progress for the next step, requested here and read there
+      if (s > 0 && seen < BG_DONE) seen = __builtin_amdgcn_readfirstlane(word_ld(prog + s - 1));
       // reflector from L's first column (lanes 0 and 32)
       float part = 0.f;
 #pragma unroll
@@ -607,7 +645,7 @@ __global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0) 
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
               const int i = 16 * h + q;
-              if (i < ln) stx(AB, (uint32_t)(s * SBW + 1 + i), L[q]);
+              if (i < ln) band_st(AB, (uint32_t)(s * SBW + 1 + i), L[q]);
             }
           }
         }
@@ -623,7 +661,7 @@ __global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0) 
 #pragma unroll
           for (int q = 0; q < 16; ++q) {
             const int c = 16 * h + q;
-            stx(AB, (uint32_t)((c0 + c) * SBW + (SB + lj - c)), tbw[lj * (SB + 1) + c]);
+            band_st(AB, (uint32_t)((c0 + c) * SBW + (SB + lj - c)), tbw[lj * (SB + 1) + c]);
           }
         }
         wave_sync();
@@ -648,7 +686,7 @@ __global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0) 
         const int c = 16 * h + q, i = c + lj;
         if (i < ln) {
           D[q] = fmaf(-vbw[i], wbw[c], fmaf(-wbw[i], vbw[c], D[q]));
-          stx(AB, (uint32_t)((r0 + c) * SBW + lj), D[q]);
+          band_st(AB, (uint32_t)((r0 + c) * SBW + lj), D[q]);
         }
       }
       // E <- E H (row layout: lane (i, h) holds columns 16 h ..)
@@ -669,26 +707,29 @@ __global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0) 
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
           const int c = 16 * h + q;
-          if (c < ln) stx(AB, (uint32_t)((r0 + c) * SBW + (ln - c)), E[q]);
+          if (c < ln) band_st(AB, (uint32_t)((r0 + c) * SBW + (ln - c)), E[q]);
         }
       }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-      if (lane == 0) __hip_atomic_store(&prog[wv], s * 1024 + k + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       if (ne < 2) break;
       r0 = r1;
     }
     if (stop) {
-      if (lane == 0) __hip_atomic_store(&abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (lane == 0) word_st(words + 1, 1);
       break;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    if (lane == 0) __hip_atomic_store(&prog[wv], s * 1024 + 1023, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (lane == 0) word_st(prog + s, BG_DONE);
   }
-  __syncthreads();
-  const bool bad = abort_flag != 0;
-  for (int i = tid; i < n; i += BG_WAVES * 64) {
-    M.d[i] = bad ? __builtin_nan("") : (double)AB[(int64_t)i * SBW];
-    M.e[i] = (i + 1 < n) ? (double)AB[(int64_t)i * SBW + 1] : 0.0;
+}
+
+// the tridiagonal out of the band (NaN on the diagonal of a chase that gave up)
+__global__ void __launch_bounds__(256) k_sb_bulge_finish(SbArgs a, int mat0) {
+  const int n = a.n;
+  const SbView M = sview(a, mat0 + blockIdx.x);
+  const bool bad = bulge_words(M)[1] != 0;
+  for (int i = threadIdx.x; i < n; i += 256) {
+    M.d[i] = bad ? __builtin_nan("") : (double)M.AB[(int64_t)i * SBW];
+    M.e[i] = (i + 1 < n) ? (double)M.AB[(int64_t)i * SBW + 1] : 0.0;
   }
 }
 
@@ -1030,7 +1071,11 @@ hipError_t launch_sb_reduce(const EigBatch &b, float *work, const GemmProblem *t
     hipError_t e = launch_update3(tab_dev + (size_t)p * b.n_mat + m0, nm, m, st);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_sb_bulge, dim3(nm), dim3(BG_WAVES * 64), 0, st, a, m0);
+  // enough wavefronts for the sweeps that can be in flight
+  const int groups = std::max(1, std::min(8, (n + 511) / 512));
+  hipLaunchKernelGGL(k_sb_bulge_clear, dim3(nm), dim3(256), 0, st, a, m0);
+  hipLaunchKernelGGL(k_sb_bulge, dim3(nm * groups), dim3(BG_WAVES * 64), 0, st, a, m0, groups);
+  hipLaunchKernelGGL(k_sb_bulge_finish, dim3(nm), dim3(256), 0, st, a, m0);
   return hipGetLastError();
 }
 

@@ -96,13 +96,6 @@ JOLT_DEV float fold16(float a, float b) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// 1/x: the hardware estimate and two Newton steps
-JOLT_DEV double recip2(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(r, fma(-x, r, 1.0), r);
-  return fma(r, fma(-x, r, 1.0), r);
-}
-
 // CC: columns per lane (n <= 64 CC); TW: waves per matrix; RW: rows per wave (n <= TW RW);
 // NW: waves per workgroup (TW / NW workgroups per matrix)
 template <int CC, int TW, int RW, int NW>
