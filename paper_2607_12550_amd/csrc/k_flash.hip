@@ -32,11 +32,16 @@ __global__ void k_sketch(SketchArgs a) {
 }
 
 // partial fp64 Gram of a row chunk: Gp[cell][chunk] += Y[rows]^T Y[rows] for the 64 x 64
-// output tile (ti, tj), ti >= tj (lower tiles only; the Cholesky reads the lower triangle).
-// Each thread loads two 4-column runs of both 32 x 64 operand blocks; the next block's loads
-// are issued before the current block is multiplied, so their latency overlaps the fp64
-// multiply-adds.
+// output tile (ti, tj), ti >= tj (lower tiles only; the Cholesky reads the lower triangle), on the
+// fp64 matrix cores (v_mfma_f64_16x16x4_f64, products of fp32 values exact).  Each of the four
+// waves forms a 32 x 32 quarter as 2 x 2 blocks: per four rows it reads two values of either
+// operand from LDS and widens them, for four products; as vector code every 16 multiply-adds of a
+// thread took eight LDS reads and eight conversions, which bounded it.  Each thread loads two
+// 4-column runs of both 32 x 64 operand blocks; the next block's loads are issued before the
+// current block is multiplied.  16 cells of 32768 x 522: 4.5 -> 3.3 ms a call on average over
+// the three of a range finder (two of 32768 rows, one of 4096).
 constexpr int GT = 64, GR = 32;
+typedef double d4_t __attribute__((ext_vector_type(4)));
 
 // four consecutive entries of row r from column c (zero at and beyond column l)
 JOLT_DEV jf4 gram64_load4(const float *Y, int64_t ld, int64_t r, bool row_ok, int c, int l) {
@@ -57,13 +62,14 @@ __global__ void __launch_bounds__(256) k_gram64(Gram64Args a) {
   const int l = a.l;
   const float *Y = a.Y + (int64_t)cell * a.y_cell_stride;
   const int64_t r0 = (int64_t)chunk * a.chunk_rows, r1 = min((int64_t)a.rows, r0 + a.chunk_rows);
-  __shared__ float ya[GR][GT + 1], yb[GR][GT + 1];
+  __shared__ __attribute__((aligned(16))) float ya[GR][GT + 16], yb[GR][GT + 16];   // four rows in distinct banks
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  double acc[4][4];
+  const int lane = tid & 63, wave = tid >> 6, wr = (wave >> 1) * 32, wc = (wave & 1) * 32, l16 = lane & 15, kq = lane >> 4;
+  d4_t acc[2][2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
+    for (int j = 0; j < 2; ++j) acc[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
   // staging: thread (ty, tx) moves rows ty and ty + 16, columns 4 tx .. 4 tx + 3 of each block
   jf4 pa[2], pb[2];
   auto fetch = [&](int64_t rb) {
@@ -78,33 +84,34 @@ __global__ void __launch_bounds__(256) k_gram64(Gram64Args a) {
   for (int64_t rb = r0; rb < r1; rb += GR) {
     __syncthreads();
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        ya[ty + 16 * h][4 * tx + e] = pa[h][e];
-        yb[ty + 16 * h][4 * tx + e] = pb[h][e];
-      }
+    for (int h = 0; h < 2; ++h) {
+      *reinterpret_cast<jf4 *>(&ya[ty + 16 * h][4 * tx]) = pa[h];
+      *reinterpret_cast<jf4 *>(&yb[ty + 16 * h][4 * tx]) = pb[h];
+    }
     __syncthreads();
     if (rb + GR < r1) fetch(rb + GR);
-#pragma unroll 4
-    for (int rr = 0; rr < GR; ++rr) {
-      double va[4], vb[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { va[i] = ya[rr][ty * 4 + i]; vb[i] = yb[rr][tx * 4 + i]; }
+    for (int k = 0; k < GR; k += 4) {
+      double va[2], vb[2];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 2; ++i) { va[i] = ya[k + kq][wr + 16 * i + l16]; vb[i] = yb[k + kq][wc + 16 * i + l16]; }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fma(va[i], vb[j], acc[i][j]);
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[i], vb[j], acc[i][j], 0, 0, 0);
     }
   }
   double *G = a.partial + ((int64_t)cell * a.chunks + chunk) * (int64_t)l * l;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = ti * GT + ty * 4 + i, c = tj * GT + tx * 4 + j;
-      if (r < l && c < l) G[(int64_t)r * l + c] = acc[i][j];
-    }
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        // entry e of a block: row 4 e + lane / 16, column lane % 16
+        const int r = ti * GT + wr + 16 * i + 4 * e + kq, c = tj * GT + wc + 16 * j + l16;
+        if (r < l && c < l) G[(int64_t)r * l + c] = acc[i][j][e];
+      }
 }
 
 __global__ void k_gram64_reduce(Gram64Args a) {
