@@ -31,13 +31,30 @@ JOLT_HD float bf16_to_f32(bf16_t b) {
   return f;
 }
 
-// fp32 -> bf16, round to nearest even (NaN stays NaN)
+// fp32 -> bf16, round to nearest even (NaN stays NaN); on the device the conversion instruction
 JOLT_HD bf16_t f32_to_bf16(float f) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const __bf16 h = (__bf16)f;
+  bf16_t b;
+  __builtin_memcpy(&b, &h, 2);
+  return b;
+#else
   uint32_t u;
   __builtin_memcpy(&u, &f, 4);
   if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)0x7fc0;
   u += 0x7fffu + ((u >> 16) & 1u);
   return (bf16_t)(u >> 16);
+#endif
+}
+
+// two fp32 -> bf16 in one word, a in the low half (one instruction)
+JOLT_DEV uint32_t pack_bf16(float a, float b) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  const b2 h = __builtin_convertvector((f2){a, b}, b2);
+  uint32_t w;
+  __builtin_memcpy(&w, &h, 4);
+  return w;
 }
 
 // fp64 -> bf16 with a single round to nearest even (no intermediate fp32 rounding).

@@ -934,8 +934,7 @@ __global__ void __launch_bounds__(NT, sizeof(TIO) == 2 ? 2 : 1) k_core(FusedArgs
     for (int u = 0; u < NU; ++u) {
       uint8_t *dst = sh + trow * L::IO_ROW + (8 * u + 4 * h) * (int)sizeof(TIO);
       if constexpr (sizeof(TIO) == 2) {
-        const uint32_t w0 = (uint32_t)f32_to_bf16(v[4 * u]) | ((uint32_t)f32_to_bf16(v[4 * u + 1]) << 16);
-        const uint32_t w1 = (uint32_t)f32_to_bf16(v[4 * u + 2]) | ((uint32_t)f32_to_bf16(v[4 * u + 3]) << 16);
+        const uint32_t w0 = pack_bf16(v[4 * u], v[4 * u + 1]), w1 = pack_bf16(v[4 * u + 2], v[4 * u + 3]);
         *reinterpret_cast<uint2 *>(dst) = make_uint2(w0, w1);
       } else {
         *reinterpret_cast<float4 *>(dst) = make_float4(v[4 * u], v[4 * u + 1], v[4 * u + 2], v[4 * u + 3]);
@@ -1376,8 +1375,8 @@ __global__ void __launch_bounds__(CW_NT, 1) k_core_w(FusedArgs a) {
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
           const int u = 2 * k + e;
-          w[2 * e] = (uint32_t)f32_to_bf16(v[4 * u]) | ((uint32_t)f32_to_bf16(v[4 * u + 1]) << 16);
-          w[2 * e + 1] = (uint32_t)f32_to_bf16(v[4 * u + 2]) | ((uint32_t)f32_to_bf16(v[4 * u + 3]) << 16);
+          w[2 * e] = pack_bf16(v[4 * u], v[4 * u + 1]);
+          w[2 * e + 1] = pack_bf16(v[4 * u + 2], v[4 * u + 3]);
           if constexpr (!ROPE) { const uint2 mk = mask[u]; w[2 * e] ^= mk.x; w[2 * e + 1] ^= mk.y; }
         }
         pair_exchange(w[0], w[2]);         // unit 2 k to the lower lane, 2 k + 1 to the upper

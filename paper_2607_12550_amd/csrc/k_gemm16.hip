@@ -52,9 +52,14 @@ JOLT_DEV int64_t opoff(const GemmOperand &op, int row, int col) {
   return (int64_t)row * op.ld + operand_col(op, col);
 }
 
-JOLT_DEV void split_bf16(float x, uint16_t &h, uint16_t &l) {
-  h = f32_to_bf16(x);
-  l = f32_to_bf16(x - bf16_to_f32(h));
+// the bf16 terms hi and lo of two values, one word each.  The conversion instruction does in six
+// operations what rounding in integer arithmetic took some 26 for: at 128 x 128 tiles with one
+// split operand those were more vector cycles per K step (about 1660) than its products (1024).
+// 16 cells of 32768 x 4096 x 522: X Q' 8.9 -> 7.5 ms, the orthonormaliser's products 1.59 -> 1.16
+// ms each, its split Gram 1.09 -> 0.89 ms.
+JOLT_DEV void split2_bf16(float x, float y, uint32_t &h, uint32_t &l) {
+  h = pack_bf16(x, y);
+  l = pack_bf16(x - __uint_as_float(h << 16), y - __uint_as_float(h & 0xffff0000u));
 }
 
 // 8 elements as loaded: bf16 bits in four 32-bit words, or two float4
@@ -91,8 +96,6 @@ JOLT_DEV void load8(const GemmOperand &op, int row, int col, int nrows, int ncol
     }
   }
 }
-
-JOLT_DEV uint32_t pk(uint16_t a, uint16_t b) { return (uint32_t)a | ((uint32_t)b << 16); }
 
 // Staging of one R (m or n) x 64 (k) operand tile through registers.
 //   k-contiguous: unit u = tid + 256 q: row u / 8, k run (u % 8) * 8 (8 lanes per 128-byte row);
@@ -164,24 +167,21 @@ struct Addr {
   JOLT_DEV float elem_f(const Stage<R, KC, F32> &s, int q, int e) const {
     return e < 4 ? s.v[q].a[e] : s.v[q].b[e - 4];
   }
-  JOLT_DEV uint16_t elem_h(const Stage<R, KC, F32> &s, int q, int e) const {
-    return (uint16_t)(s.v[q].w[e >> 1] >> (16 * (e & 1)));
-  }
 
   JOLT_DEV void stash(const Stage<R, KC, F32> &s, uint16_t *hi, uint16_t *lo, int tid) const {
     if constexpr (KC) {
 #pragma unroll
       for (int q = 0; q < NV; ++q) {
         const int u = tid + NT * q, r = u >> 3, kc = (u & 7) * 8;
-        uint16_t h[8], l[8];
+        if constexpr (F32) {
+          uint32_t h[4], l[4];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          if constexpr (F32) split_bf16(elem_f(s, q, i), h[i], l[i]);
-          else h[i] = elem_h(s, q, i);
+          for (int i = 0; i < 4; ++i) split2_bf16(elem_f(s, q, 2 * i), elem_f(s, q, 2 * i + 1), h[i], l[i]);
+          *reinterpret_cast<uint4 *>(hi + r * LDK + kc) = make_uint4(h[0], h[1], h[2], h[3]);
+          *reinterpret_cast<uint4 *>(lo + r * LDK + kc) = make_uint4(l[0], l[1], l[2], l[3]);
+        } else {
+          *reinterpret_cast<ju4 *>(hi + r * LDK + kc) = s.v[q].w;
         }
-        *reinterpret_cast<uint4 *>(hi + r * LDK + kc) = make_uint4(pk(h[0], h[1]), pk(h[2], h[3]), pk(h[4], h[5]), pk(h[6], h[7]));
-        if constexpr (F32)
-          *reinterpret_cast<uint4 *>(lo + r * LDK + kc) = make_uint4(pk(l[0], l[1]), pk(l[2], l[3]), pk(l[4], l[5]), pk(l[6], l[7]));
       }
     } else {
 #pragma unroll
@@ -189,15 +189,15 @@ struct Addr {
         const int b = tid + NT * p, kb = (b & 15) * 4, mb = (b >> 4) * 8;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          uint16_t h[4], l[4];
+          uint32_t h[2], l[2];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            if constexpr (F32) split_bf16(elem_f(s, 4 * p + q, e), h[q], l[q]);
-            else h[q] = elem_h(s, 4 * p + q, e);
+          for (int q = 0; q < 2; ++q) {
+            if constexpr (F32) split2_bf16(elem_f(s, 4 * p + 2 * q, e), elem_f(s, 4 * p + 2 * q + 1, e), h[q], l[q]);
+            else h[q] = __builtin_amdgcn_perm(s.v[4 * p + 2 * q + 1].w[e >> 1], s.v[4 * p + 2 * q].w[e >> 1],
+                                              e & 1 ? 0x07060302u : 0x05040100u);
           }
-          *reinterpret_cast<uint2 *>(hi + (mb + e) * LDK + kb) = make_uint2(pk(h[0], h[1]), pk(h[2], h[3]));
-          if constexpr (F32)
-            *reinterpret_cast<uint2 *>(lo + (mb + e) * LDK + kb) = make_uint2(pk(l[0], l[1]), pk(l[2], l[3]));
+          *reinterpret_cast<uint2 *>(hi + (mb + e) * LDK + kb) = make_uint2(h[0], h[1]);
+          if constexpr (F32) *reinterpret_cast<uint2 *>(lo + (mb + e) * LDK + kb) = make_uint2(l[0], l[1]);
         }
       }
     }
@@ -569,13 +569,6 @@ struct U3Lds {
   uint16_t a[3][U3_BM * U3_LDK], b[3][U3_BM * U3_LDK];   // 61.4 KB
 };
 
-JOLT_DEV void split3_bf16(float x, uint16_t &h, uint16_t &m, uint16_t &l) {
-  h = f32_to_bf16(x);
-  const float r1 = x - bf16_to_f32(h);                   // exact
-  m = f32_to_bf16(r1);
-  l = f32_to_bf16(r1 - bf16_to_f32(m));                  // exact difference, rounded once
-}
-
 // the thread's 4 (k) x 8 (mn) block of an mn-contiguous operand, zero outside K x MN
 JOLT_DEV void load_block_mn(const GemmOperand &op, int k0, int mn0, int K, int MN, bool vec, float (&v)[4][8]) {
   const float *base = reinterpret_cast<const float *>(op.ptr);
@@ -599,13 +592,18 @@ JOLT_DEV void stash3(const float (&v)[4][8], uint16_t *p0, uint16_t *p1, uint16_
   // kb: the block's first k within the LDS half
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    uint16_t h[4], m[4], l[4];
+    uint32_t h[2], m[2], l[2];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) split3_bf16(v[kk][e], h[kk], m[kk], l[kk]);
+    for (int kk = 0; kk < 2; ++kk) {
+      // exact differences, each term rounded once
+      const float x = v[2 * kk][e], y = v[2 * kk + 1][e];
+      h[kk] = pack_bf16(x, y);
+      split2_bf16(x - __uint_as_float(h[kk] << 16), y - __uint_as_float(h[kk] & 0xffff0000u), m[kk], l[kk]);
+    }
     const int o = (mn + e) * U3_LDK + kb;
-    *reinterpret_cast<uint2 *>(p0 + o) = make_uint2(pk(h[0], h[1]), pk(h[2], h[3]));
-    *reinterpret_cast<uint2 *>(p1 + o) = make_uint2(pk(m[0], m[1]), pk(m[2], m[3]));
-    *reinterpret_cast<uint2 *>(p2 + o) = make_uint2(pk(l[0], l[1]), pk(l[2], l[3]));
+    *reinterpret_cast<uint2 *>(p0 + o) = make_uint2(h[0], h[1]);
+    *reinterpret_cast<uint2 *>(p1 + o) = make_uint2(m[0], m[1]);
+    *reinterpret_cast<uint2 *>(p2 + o) = make_uint2(l[0], l[1]);
   }
 }
 
