@@ -33,6 +33,7 @@
 #include "common.h"
 #include "kernels.h"
 #include <algorithm>
+#include <type_traits>
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
@@ -55,7 +56,7 @@ JOLT_DEV int64_t opoff(const GemmOperand &op, int row, int col) {
 // the bf16 terms hi and lo of two values, one word each.  The conversion instruction does in six
 // operations what rounding in integer arithmetic took some 26 for: at 128 x 128 tiles with one
 // split operand those were more vector cycles per K step (about 1660) than its products (1024).
-// 16 cells of 32768 x 4096 x 522: X Q' 8.9 -> 7.5 ms, the orthonormaliser's products 1.59 -> 1.16
+// 16 cells of 32768 x 4096 x 522: X Q' 8.9 -> 7.5 ms (7.0 without the empty columns' work), the orthonormaliser's products 1.59 -> 1.16
 // ms each, its split Gram 1.09 -> 0.89 ms.
 JOLT_DEV void split2_bf16(float x, float y, uint32_t &h, uint32_t &l) {
   h = pack_bf16(x, y);
@@ -355,14 +356,18 @@ __global__ void __launch_bounds__(NT) k_gemm16(const GemmProblem *__restrict__ p
   const int kfull = P.K & ~(BK - 1);
 #define MM_FETCH(s, k) do { const int k_ = (k); \
     if (k_ < kfull) { ad_a.fetch_full(P.A, k_, sa[s]); ad_b.fetch_full(P.B, k_, sb[s]); } } while (0)
-  auto compute_at = [&](int buf) {
+  // The last tile column may hold few columns (522 = 4 * 128 + 10 for FlashJoLT's default rank):
+  // its waves multiply only the 32-column blocks that exist, 15% of such a product's work.
+  const int nbv = min(NI, max(0, (P.N - n0 - wn * (BN / 2) + 31) / 32));
+  auto compute_n = [&](int buf, auto nb_) {
+    constexpr int NB = decltype(nb_)::value;
     const uint16_t *la_ = sm.a + buf * LA, *lb_ = sm.b + buf * LB;
     // 16-wide k steps; with 256 x 256 tiles they are not unrolled, so that the fragments of
     // one step only are live beside the 256 accumulator registers
 #pragma unroll (BN == 256 ? 1 : BK / 16)
     for (int s = 0; s < BK / 16; ++s) {
       const int ko = s * 16 + 8 * lh;
-      bf16x8_t fa[MI], fb[NI], la[MI], lb[NI];
+      bf16x8_t fa[MI], fb[NB], la[MI], lb[NB];
 #pragma unroll
       for (int a = 0; a < MI; ++a) {
         const int ra = (wm * (BM / 2) + a * 32 + lr) * LDK + ko;
@@ -370,7 +375,7 @@ __global__ void __launch_bounds__(NT) k_gemm16(const GemmProblem *__restrict__ p
         if constexpr (AS) la[a] = *reinterpret_cast<const bf16x8_t *>(la_ + TA + ra);
       }
 #pragma unroll
-      for (int b = 0; b < NI; ++b) {
+      for (int b = 0; b < NB; ++b) {
         const int rb = (wn * (BN / 2) + b * 32 + lr) * LDK + ko;
         fb[b] = *reinterpret_cast<const bf16x8_t *>(lb_ + rb);
         if constexpr (BS) lb[b] = *reinterpret_cast<const bf16x8_t *>(lb_ + TB + rb);
@@ -378,12 +383,17 @@ __global__ void __launch_bounds__(NT) k_gemm16(const GemmProblem *__restrict__ p
 #pragma unroll
       for (int a = 0; a < MI; ++a)
 #pragma unroll
-        for (int b = 0; b < NI; ++b) {
+        for (int b = 0; b < NB; ++b) {
           acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
           if constexpr (AS) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(la[a], fb[b], acc[a][b], 0, 0, 0);
           if constexpr (BS) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], lb[b], acc[a][b], 0, 0, 0);
         }
     }
+  };
+  auto compute_at = [&](int buf) {
+    if (nbv == NI) compute_n(buf, std::integral_constant<int, NI>{});
+    else if (nbv > 0 && NI == 2) compute_n(buf, std::integral_constant<int, 1>{});
+    else if (nbv > 0) compute_n(buf, std::integral_constant<int, NI>{});
   };
   if constexpr (Lds<BM, BN, AS, BS>::DB) {
   // two LDS buffers: tile k+1 is stored into one while tile k is multiplied out of the
@@ -807,19 +817,19 @@ bool gemm16_prepare(GemmProblem *probs, int n, int &ta, int &tb, bool &ak, bool 
     lower = lower || p.lower_only;
   }
   if (swap) { std::swap(ta, tb); std::swap(ak, bk); }
-  // 256-row tiles for split-operand products over long M whose bf16 operand is k-contiguous
-  // (two LDS buffers still fit); 256 x 256 tiles for large lower-triangle bf16 tables with a
-  // long K (the token Gram of wide cells: each K step moves 512 operand rows for 256 x 256
+  // 256-row tiles for products of a bf16 operand over long M and a split one: the K loop is bound
+  // by LDS bandwidth, and a wave's 128 x 64 block reads eight fragments per 16 products where its
+  // 64 x 64 block reads six per eight (X^T Q and Q^T X of 16 cells at T = 32768: 8.9 ms with
+  // 128 rows, 7.6 with 256; X Q': 7.0); 256 x 256 tiles for large lower-triangle bf16 tables with
+  // a long K (the token Gram of wide cells: each K step moves 512 operand rows for 256 x 256
   // outputs, and each wave's 128 x 128 block reads 8 fragments per 16 MFMAs, where the
   // 128 x 128 tiles read 4 per 4 and leave the K loop bound by LDS bandwidth); 128 otherwise
-  // (an m-contiguous bf16 operand is transposed on its way to LDS, and the 128-row tile
-  // then runs two workgroups per CU; at K = 4096 the 128-row tiles also keep two
-  // workgroups per CU busy and measured faster)
+  // (at K = 4096 two workgroups of 128-row tiles per CU measured faster)
   const bool bf_both = ta == GT_BF16 && tb == GT_BF16 && ak && bk;
   bool k64 = true;
   for (int i = 0; i < n; ++i) k64 = k64 && probs[i].K % BK == 0;
   if (lower && bf_both && k64 && maxM >= 2048 && minK >= 16384) bm = GEMM16_SQUARE256;
-  else bm = (tb == GT_F32 && ta == GT_BF16 && maxM >= 2048 && !lower && ak) ? 256 : 128;
+  else bm = (tb == GT_F32 && ta == GT_BF16 && maxM >= 2048 && !lower) ? 256 : 128;
   return true;
 }
 
