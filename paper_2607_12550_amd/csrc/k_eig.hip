@@ -401,7 +401,10 @@ __global__ void k_z_to_f32(EigBatch b, InvitWork w, int kmax, float *U, int64_t 
 
 // T factor of the block reflector of panel p (columns i0 .. i0+pw-1 of A):
 // H_i0 ... H_{i0+pw-1} = I - V T V^T with T upper triangular, built by the forward
-// recurrence T[0:j, j] = -tau_j T[0:j, 0:j] (V^T V)[0:j, j] from the precomputed Gram S.
+// recurrence T[a, j] = -tau_j sum_{a <= c < j} T[a, c] (V^T V)[c, j] from the precomputed Gram S.
+// Row a of T depends on no other row: thread a runs its own recurrence, without barriers, four
+// entries at a time (16-byte LDS reads, row j of the symmetric S broadcast).  A chain of
+// single multiply-adds between two barriers per column took 350 us a panel, this 132 us.
 constexpr int NB = 128;
 __global__ void __launch_bounds__(NB) k_larft(EigBatch b, const float *S_all, float *Tout) {
   const int mat = blockIdx.y, p = blockIdx.x, n = b.n;
@@ -410,30 +413,36 @@ __global__ void __launch_bounds__(NB) k_larft(EigBatch b, const float *S_all, fl
   const int pw = max(0, min(NB, n - refl_off(b) - i0));
   const float *tau = b.tau + (int64_t)mat * n;
   const float *S = S_all + ((int64_t)mat * panels + p) * NB * NB;
-  __shared__ float T[NB][NB + 1];
-  __shared__ float Ss[NB][NB + 1];              // the panel's Gram, staged once
+  extern __shared__ __attribute__((aligned(16))) float larft_lds[];
+  float (*T)[NB + 4] = reinterpret_cast<float (*)[NB + 4]>(larft_lds);
+  float (*Ss)[NB + 4] = T + NB;                 // the panel's Gram, staged once
   const int a = threadIdx.x;
-  for (int c = 0; c < NB; ++c) T[a][c] = 0.f;
+  for (int c = 0; c < NB; ++c) T[c][a] = 0.f;
   for (int r0 = 0; r0 < NB; r0 += 16) {         // sixteen loads in flight per thread
     float x[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) x[k] = S[(r0 + k) * NB + a];
+    // entries past a short panel's width are not part of the Gram
 #pragma unroll
-    for (int k = 0; k < 16; ++k) Ss[r0 + k][a] = x[k];
+    for (int k = 0; k < 16; ++k) Ss[r0 + k][a] = r0 + k < pw && a < pw ? x[k] : 0.f;
   }
   __syncthreads();
   for (int j = 0; j < pw; ++j) {
     const float tj = tau[i0 + j];
-    float s = 0.f;
-    if (a < j)
-      for (int c = a; c < j; ++c) s = fmaf(T[a][c], Ss[c][j], s);
-    __syncthreads();
-    if (a < j) T[a][j] = -tj * s;
+    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+    if (a < j) {
+      // T[a][c] is zero for c < a and, so far, for c >= j
+      for (int c = a & ~3; c < j; c += 4) {
+        const float4 t = *reinterpret_cast<const float4 *>(&T[a][c]), g = *reinterpret_cast<const float4 *>(&Ss[j][c]);
+        s0 = fmaf(t.x, g.x, s0); s1 = fmaf(t.y, g.y, s1); s2 = fmaf(t.z, g.z, s2); s3 = fmaf(t.w, g.w, s3);
+      }
+      T[a][j] = -tj * ((s0 + s1) + (s2 + s3));
+    }
     if (a == j) T[j][j] = tj;
-    __syncthreads();
   }
+  __syncthreads();
   float *To = Tout + ((int64_t)mat * panels + p) * NB * NB;
-  for (int c = 0; c < NB; ++c) To[a * NB + c] = T[a][c];
+  for (int c = 0; c < NB; ++c) To[c * NB + a] = T[c][a];
 }
 
 }  // namespace
@@ -553,7 +562,11 @@ hipError_t launch_backtransform(const EigBatch &b, const InvitWork &w, int kmax,
   if (err != hipSuccess) return err;
   err = launch_gemm(tab_dev, nm * panels, NB, NB, 1, GT_F32, GT_F32, false, false, st);
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(k_larft, dim3(panels, nm), dim3(NB), 0, st, b, Sf, Tf);
+  constexpr size_t larft_bytes = (size_t)2 * NB * (NB + 4) * sizeof(float);
+  err = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_larft), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)larft_bytes);
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL(k_larft, dim3(panels, nm), dim3(NB), larft_bytes, st, b, Sf, Tf);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   for (int p = panels - 1; p >= 0; --p) {
