@@ -230,18 +230,42 @@ __global__ void __launch_bounds__(CB) k_chol_diag(CholArgs a, int kb) {
   }
 }
 
-// 4 x 4 outputs per thread of a 64 x 64 tile: acc[r][c] += sum_k A[r][k] B[c][k]
-JOLT_DEV void tile_mma_nt(double (&acc)[4][4], const double (*A)[CLD], const double (*B)[CLD], int k0, int k1) {
-  const int r0 = (threadIdx.x >> 4) * 4, c0 = (threadIdx.x & 15) * 4;
-  for (int k = k0; k < k1; ++k) {
-    double av[4], bv[4];
+// acc += A B^T of two 64 x 64 tiles on the fp64 matrix cores, a 32 x 32 quarter per wave as 2 x 2
+// blocks (as vector code the LDS reads of 16 multiply-adds bounded it: a block row of the inverse
+// of 16 cells took 45 us, now 25); tile_each hands every output (row, column, value) of the tile to f.
+struct TileAcc {
+  d4_t v[2][2];
+  JOLT_DEV void clear() {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { av[i] = A[r0 + i][k]; bv[i] = B[c0 + i][k]; }
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) acc[i][c] = fma(av[i], bv[c], acc[i][c]);
+      for (int j = 0; j < 2; ++j) v[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
   }
+};
+JOLT_DEV void tile_mma_nt(TileAcc &acc, const double (*A)[CLD], const double (*B)[CLD]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
+  const int r0 = (wave >> 1) * 32 + l16, c0 = (wave & 1) * 32 + l16;
+#pragma unroll 4
+  for (int k = kq; k < CB; k += 4) {
+    double av[2], bv[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) { av[i] = A[r0 + 16 * i][k]; bv[i] = B[c0 + 16 * i][k]; }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc.v[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], bv[j], acc.v[i][j], 0, 0, 0);
+  }
+}
+template <class F>
+JOLT_DEV void tile_each(const TileAcc &acc, F f) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        f((wave >> 1) * 32 + 16 * i + 4 * e + kq, (wave & 1) * 32 + 16 * j + l16, acc.v[i][j][e]);
 }
 
 __global__ void __launch_bounds__(256) k_chol_panel(CholArgs a, int kb) {
@@ -252,16 +276,13 @@ __global__ void __launch_bounds__(256) k_chol_panel(CholArgs a, int kb) {
   tile_load(ta, G, l, I * CB, kb * CB);
   for (int q = threadIdx.x; q < CB * CB; q += 256) td[q / CB][q % CB] = D[q];
   __syncthreads();
-  double acc[4][4] = {};
-  tile_mma_nt(acc, ta, td, 0, CB);             // L_I,kb = G_I,kb D^T
-  const int r0 = (threadIdx.x >> 4) * 4, c0 = (threadIdx.x & 15) * 4;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int r = I * CB + r0 + i, cc = kb * CB + c0 + c;
-      if (r < l && cc < l) G[(int64_t)r * l + cc] = acc[i][c];
-    }
+  TileAcc acc;
+  acc.clear();
+  tile_mma_nt(acc, ta, td);                    // L_I,kb = G_I,kb D^T
+  tile_each(acc, [&](int i, int c, double v) {
+    const int r = I * CB + i, cc = kb * CB + c;
+    if (r < l && cc < l) G[(int64_t)r * l + cc] = v;
+  });
 }
 
 __global__ void __launch_bounds__(256) k_chol_update(CholArgs a, int kb) {
@@ -274,16 +295,13 @@ __global__ void __launch_bounds__(256) k_chol_update(CholArgs a, int kb) {
   tile_load(ta, G, l, I * CB, kb * CB);
   tile_load(tb, G, l, J * CB, kb * CB);
   __syncthreads();
-  double acc[4][4] = {};
-  tile_mma_nt(acc, ta, tb, 0, CB);
-  const int r0 = (threadIdx.x >> 4) * 4, c0 = (threadIdx.x & 15) * 4;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int r = I * CB + r0 + i, cc = J * CB + c0 + c;
-      if (r < l && cc < l) G[(int64_t)r * l + cc] -= acc[i][c];
-    }
+  TileAcc acc;
+  acc.clear();
+  tile_mma_nt(acc, ta, tb);
+  tile_each(acc, [&](int i, int c, double v) {
+    const int r = I * CB + i, cc = J * CB + c;
+    if (r < l && cc < l) G[(int64_t)r * l + cc] -= v;
+  });
 }
 
 // block row I of M = L^-1: M_IJ = -D_I sum_{K=J}^{I-1} L_IK M_KJ for every J < I
@@ -293,8 +311,8 @@ __global__ void __launch_bounds__(256) k_chol_inv_row(CholArgs a, int I) {
   double *M = a.M + (int64_t)cell * l * l;
   const double *D = a.Dinv + ((int64_t)cell * a.nbk + I) * CB * CB;
   __shared__ double ta[CB][CLD], tb[CB][CLD];
-  const int r0 = (threadIdx.x >> 4) * 4, c0 = (threadIdx.x & 15) * 4;
-  double acc[4][4] = {};
+  TileAcc acc;
+  acc.clear();
   // the tiles of step K + 1 (L_I,K+1 and M_K+1,J) are loaded into registers while step K
   // is multiplied; thread element h is entry (q / CB, q % CB), q = tid + 256 h, of each tile
   constexpr int PE = CB * CB / 256;
@@ -319,25 +337,20 @@ __global__ void __launch_bounds__(256) k_chol_inv_row(CholArgs a, int I) {
     }
     __syncthreads();
     if (K + 1 < I) fetch(K + 1);
-    tile_mma_nt(acc, ta, tb, 0, CB);
+    tile_mma_nt(acc, ta, tb);
   }
   __syncthreads();
   // S = acc -> tb (transposed, tb[c][k] = S[k][c]); D_I -> ta
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) tb[c0 + c][r0 + i] = acc[i][c];
+  tile_each(acc, [&](int i, int c, double v) { tb[c][i] = v; });
   for (int q = threadIdx.x; q < CB * CB; q += 256) ta[q / CB][q % CB] = D[q];
   __syncthreads();
-  double out[4][4] = {};
-  tile_mma_nt(out, ta, tb, 0, CB);
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int r = I * CB + r0 + i, cc = J * CB + c0 + c;
-      if (r < l && cc < l) M[(int64_t)r * l + cc] = -out[i][c];
-    }
+  TileAcc out;
+  out.clear();
+  tile_mma_nt(out, ta, tb);
+  tile_each(out, [&](int i, int c, double v) {
+    const int r = I * CB + i, cc = J * CB + c;
+    if (r < l && cc < l) M[(int64_t)r * l + cc] = -v;
+  });
 }
 
 // Rinv = M^T in fp32 (l x ldr), zero above the diagonal of M and in the padding columns
