@@ -360,7 +360,7 @@ hipError_t launch_reg(const EigBatch &b, int spin_max, hipStream_t st) {
 int trd_reg_workgroups(int n) { return n <= 256 ? 1 : n <= 576 ? 8 : n <= 768 ? 16 : 32; }
 
 hipError_t launch_trd_reg(const EigBatch &b, int spin_max, hipStream_t st) {
-  const int n = b.n, spin = std::min(spin_max, 1 << 20);
+  const int n = b.n, spin = std::max(spin_max, 0);
   if (n < 1 || n > TRD_REG_MAX) return hipErrorInvalidValue;
   // up to n = 256 one workgroup (an exchange between workgroups costs what its compute does)
   if (n <= 64) return launch_reg<1, 8, 8, 8>(b, spin, st);

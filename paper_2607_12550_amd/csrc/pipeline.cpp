@@ -356,7 +356,7 @@ struct CallChecks {
   int nc = 0, n_orth = 0;
   bool spectrum = false;
   std::vector<int32_t> bad, clamp, tstat, fstat;
-  std::vector<double> E, d0;   // d0: first diagonal entry of each two-stage tridiagonal
+  std::vector<double> E, d0;   // d0: a tridiagonal's entry that is NaN if its reduction gave up
 
   int queue(Run &R, int nc_, bool spectrum_computed, bool token_vecs, bool feature_vecs) {
     nc = nc_;
