@@ -517,22 +517,36 @@ __global__ void __launch_bounds__(256) k_core_prepare(const FusedCell *cells, co
   const int rT = c.rT, rd = c.rd, RD = (rd + 31) & ~31, K16 = (rT + 15) & ~15;
   const uint16_t *G = c.G + (int64_t)s * rT * rd;
   uint16_t *Gt = reinterpret_cast<uint16_t *>(c.Wt + (int64_t)s * d * c.ldw);
-  __shared__ uint16_t tile[64][130];
+  // 8 entries of a row per load and 8 of a column per store (single entries where r_d is no
+  // multiple of 8); the 64-row tile in between is transposed through LDS
+  __shared__ __attribute__((aligned(4))) uint16_t tile[64][130];
+  const bool vec = (rd & 7) == 0;
   float mx = 0.f;
   for (int i0 = 0; i0 < K16; i0 += 64) {
-    for (int q = threadIdx.x; q < 64 * RD; q += 256) {
-      const int r = q / RD, j = q - r * RD, i = i0 + r;
-      uint16_t v = 0;
-      if (i < rT && j < rd) {
-        v = G[(int64_t)i * rd + j];
-        mx = fmaxf(mx, fabsf(h_val(v)));
+    for (int q = threadIdx.x; q < 64 * (RD / 8); q += 256) {
+      const int r = q / (RD / 8), j = (q - r * (RD / 8)) * 8, i = i0 + r;
+      uint16_t v[8];
+      if (vec && i < rT && j < rd) {
+        const ju4 w = gload_u4(G + (int64_t)i * rd + j);
+        __builtin_memcpy(v, &w, 16);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = i < rT && j + e < rd ? G[(int64_t)i * rd + j + e] : (uint16_t)0;
       }
-      tile[r][j] = v;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(h_val(v[e])));
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) *reinterpret_cast<uint32_t *>(&tile[r][j + e]) = pk2(v[e], v[e + 1]);
     }
     __syncthreads();
-    for (int q = threadIdx.x; q < 64 * RD; q += 256) {
-      const int j = q / 64, r = q - j * 64;
-      if (i0 + r < K16) Gt[(int64_t)j * K16 + i0 + r] = tile[r][j];
+    for (int q = threadIdx.x; q < 8 * RD; q += 256) {
+      const int j = q >> 3, r = (q & 7) * 8;
+      if (i0 + r < K16) {
+        ju4 w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = pk2(tile[r + 2 * e][j], tile[r + 2 * e + 1][j]);
+        *reinterpret_cast<ju4 *>(Gt + (int64_t)j * K16 + i0 + r) = w;
+      }
     }
     __syncthreads();
   }
@@ -551,10 +565,11 @@ __global__ void __launch_bounds__(256) k_core_prepare(const FusedCell *cells, co
     }
     c.wexp[s] = e;
   }
-  if (s == 0) {
+  {
     // s_f U^_d[f, :] (d x r_d, fp16, rotation sign s_f folded in: an exact sign flip) with
-    // columns in stage 2's slot order, zeros past r_d
-    for (int q = threadIdx.x; q < d * RD; q += 256) {
+    // columns in stage 2's slot order, zeros past r_d; a share of it per slice (all of it in the
+    // first slice's workgroup was most of this kernel: 42 us for 16 cells x 32 slices at ranks (128, 40), 12 us shared)
+    for (int q = s * 256 + threadIdx.x; q < d * RD; q += 256 * m) {
       const int f = q / RD, p = q - f * RD;
       const int kc = p >> 4, hh = (p >> 3) & 1, sl = p & 7;
       const int jsrc = 16 * kc + 4 * hh + (sl & 3) + 8 * (sl >> 2);
@@ -982,8 +997,8 @@ __global__ void __launch_bounds__(NT, sizeof(TIO) == 2 ? 2 : 1) k_core(FusedArgs
 // RoPE: the frequencies as revolutions per token are formed once per workgroup in fp64, the
 // angle is reduced in revolutions in fp64, and cos and sin of the remaining |x| <= pi/4 are
 // Taylor polynomials in fp64 (truncation below 2^-36, under fp32's rounding).
-// 16 cells x 32 slices x 4096 tokens at ranks (128, 40), 8 bits: decode 717 us (k_core) -> 443 us,
-// 1.9 TB/s; with RoPE, 4 cells x 32 x 1777 at (96, 24), 4 bits: 156 -> 70 us.
+// 16 cells x 32 slices x 4096 tokens at ranks (128, 40), 8 bits: decode 717 us (k_core) -> 406 us,
+// 2.1 TB/s; with RoPE, 4 cells x 32 x 1777 at (96, 24), 4 bits: 156 -> 70 us.
 constexpr int CW_NT = 512;
 
 // LDS bytes for the largest U^_d and G^_s^T of a call
