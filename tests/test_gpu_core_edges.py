@@ -1,0 +1,46 @@
+"""The resident-factor decode and residual passes (bf16 caches, d >= 64) at the edges of their
+tiles: lengths around 32-token tiles and 256-token rounds, every code width and the group sizes
+one row's scales allow, ranks off the multiples of 8, and a group size that takes the staged kernel.
+
+Codes are compared stage-wise (the oracle's quantiser on the GPU's own X~, one level on at most
+1e-4 of the entries plus one entry); decoded rows with the oracle's decode of the same blob within
+one bf16 rounding (2^-8 of the entry) plus fp32 sums (1e-5 of the cell's rms).
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2607_12550_amd as J
+from gpu_util import blob_bytes, compress, ctx, decompress, device_cells
+from oracle import pipeline as opl
+from oracle.philox import rotation_signs
+from oracle.residual import quantize, rotate
+
+pytestmark = pytest.mark.gpu
+
+#     d   m  T    r_T  r_d bits group
+CASES = [(128, 2, 33, 8, 8, 8, 64), (128, 3, 257, 40, 40, 4, 128), (128, 2, 300, 136, 72, 2, 32),
+         (64, 3, 31, 16, 16, 2, 64), (64, 2, 289, 24, 8, 8, 16), (64, 4, 70, 20, 12, 4, 32),
+         (128, 1, 1, 1, 8, 4, 64), (128, 2, 100, 24, 16, 4, 16), (128, 2, 64, 0, 0, 8, 64)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "d%d_m%d_T%d_r%d_%d_b%d_g%d" % c)
+def test_codes_and_decoded_rows(case):
+    d, m, T, rT, rd, bits, group = case
+    rng = np.random.default_rng(T)
+    X = rng.standard_normal((m, T, 8)) @ rng.standard_normal((8, d)) + 0.3 * rng.standard_normal((m, T, d))
+    xs, ex, desc = device_cells([X], "bf16")
+    blobs, _ = compress(xs, desc, [J.Params(rT, rd, bits, group, J.JOLT_FACTOR_F16, 0, 9)])
+    Xt = torch.empty((m, T, d), device="cuda")
+    J.jolt_debug_export(ctx(), 2, 0, Xt)
+    Xt = Xt.cpu().numpy().astype(np.float64)
+    b = blob_bytes(blobs[0])
+    got = opl.read_blob(b)
+    codes, scales = quantize(rotate(ex[0] - Xt, rotation_signs(9, d)), bits, group)
+    diff = np.abs(np.asarray(got["codes"], dtype=np.int64).reshape(-1) - np.asarray(codes, dtype=np.int64).reshape(-1))
+    assert diff.max() <= 1 and (diff > 0).sum() <= 1 + 1e-4 * diff.size
+    np.testing.assert_allclose(np.asarray(got["scales"], dtype=np.float64).reshape(-1), np.asarray(scales, dtype=np.float64).reshape(-1), rtol=2e-3)
+    want = opl.decode_blob(b)
+    out = decompress(blobs, desc, "bf16")[0]
+    rms = np.sqrt((want ** 2).mean())
+    assert (np.abs(out - want) <= 2.0 ** -8 * np.abs(want) + 1e-5 * rms).all()
