@@ -413,8 +413,12 @@ int jolt_debug_export(jolt_ctx *ctx, int what, int cell, void *dst, size_t dst_b
  * reduction's bulge chase and, for orders 257..1024, the exchange between the workgroups that
  * hold a matrix (default 2^24 polls, range 0..2^24; 0 makes the first wait give up): a reduction
  * that gives up ends normally and the call reports JOLT_E_NOCONV, which lets that path be exercised.
+ * JOLT_DBG_TRD_GATHER bounds the polls for all workgroups of such a matrix to be running at once
+ * (default 2^16, range 0..2^24; 0 waits for none): past it one workgroup reduces the matrix, with
+ * the same accuracy.  So calls of several contexts, streams or processes may reduce side by side;
+ * at worst they slow each other down.
  * Errors: JOLT_E_INVAL. */
-enum { JOLT_DBG_INVIT_ITERS = 0, JOLT_DBG_TRD_LANES = 1, JOLT_DBG_TRD_TWO_STAGE = 2, JOLT_DBG_BULGE_SPIN = 3 };
+enum { JOLT_DBG_INVIT_ITERS = 0, JOLT_DBG_TRD_LANES = 1, JOLT_DBG_TRD_TWO_STAGE = 2, JOLT_DBG_BULGE_SPIN = 3, JOLT_DBG_TRD_GATHER = 4 };
 int jolt_debug_set(jolt_ctx *ctx, int what, int64_t value);
 
 /* Benchmark instrumentation.  When enabled, the library brackets the kernels of each

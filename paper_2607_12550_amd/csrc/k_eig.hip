@@ -30,20 +30,6 @@ JOLT_DEV double block_sum(double v, double *red) {
   return s;
 }
 
-// Workgroup sum with one barrier: successive calls alternate between two halves of red
-// (2 x waves entries), so a call never overwrites values an earlier call is still reading.
-JOLT_DEV double block_sum1(double v, double *red, int &flip) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  v = wave_sum(v);
-  double *r = red + flip * nw;
-  flip ^= 1;
-  if (lane == 0) r[wave] = v;
-  __syncthreads();
-  double s = 0.0;
-  for (int w = 0; w < nw; ++w) s += r[w];
-  return s;
-}
-
 JOLT_DEV int sturm_count(const double *d, const double *e, int n, double x, double pivmin) {
   double q = d[0] - x;
   if (fabs(q) <= pivmin) q = -pivmin;

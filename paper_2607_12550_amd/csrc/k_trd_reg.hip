@@ -25,10 +25,20 @@
 // has read column i + 1's, which every workgroup published after reading column i's.  The words
 // live in the strict upper triangle of the matrix (only the lower one is read), cleared before.
 //
-// Every wait is bounded; a workgroup that gives up leaves e[n-1] = NaN (otherwise 0), which the
-// caller reports.  A matrix's workgroups have to run together: they are neighbours in the grid,
-// which is dispatched in order, at most 32 per matrix, so the chip (256 workgroups at least)
-// always holds whole matrices and the partial ones follow as those end.
+// A matrix is reduced in registers only once all its workgroups are running: they draw (matrix,
+// part) from the launch's ticket, in order, count themselves in at the matrix's gather word, load
+// their rows and wait until the count is complete.  From there on no wait depends on anything that
+// is not running.  A workgroup whose gather wait runs out marks the matrix as left (only while the
+// count is incomplete, so all its workgroups agree), nothing has been written yet, and the
+// one-workgroup reduction behind this kernel takes it.  Kernels of other streams, contexts or
+// processes that hold the chip can therefore delay a reduction but not stop it, however the
+// workgroups are dispatched: by the ticket a launch has at most one incomplete matrix, whose up to
+// 31 waiting workgroups give their places back.  (With (matrix, part) from the block index two
+// launches could hold one XCD each with workgroups that waited for the other's; drawing them costs
+// 0.2 of 6.9 ms at n = 1001, 0.2 of 4.6 ms for 16 matrices of order 700, nothing up to 576: the
+// parts of a matrix are then spread less evenly over the XCDs.)  A second bound (spin_max) ends the exchange's own
+// waits; a workgroup that gives up there leaves e[n-1] = NaN (otherwise 0), which the caller
+// reports.
 // Whole spectrum of 4 cells, one workgroup per matrix with blocked updates -> this: T = 256 4.1 ->
 // 2.5 ms, 522 10.7 -> 5.0 ms, 700 18.1 -> 6.9 ms; against the one-stage reduction of larger
 // matrices T = 1001 21.1 -> 10.0 ms.  At n = 1300 the wave's registers spill and it loses (36 ms to
@@ -47,6 +57,27 @@ JOLT_DEV uint64_t *word_at(float *A, int n, int e) {
   const int per = (n - 20) / 2, r = e / per, k = e - r * per;
   const int64_t o = (int64_t)r * n + 17;                  // columns > r for every r < 16
   return reinterpret_cast<uint64_t *>(A + (o + ((reinterpret_cast<uintptr_t>(A) >> 2) + o) % 2)) + k;
+}
+
+// the matrix's gather word: workgroups counted in, and whether it is left to one workgroup; the
+// launch's ticket is a word of its first matrix
+constexpr uint32_t TRD_LEFT = 1u << 16;
+JOLT_DEV uint32_t *gather_word(float *A, int n) { return reinterpret_cast<uint32_t *>(word_at(A, n, 4 * n)); }
+JOLT_DEV uint32_t *ticket_word(float *A, int n) { return reinterpret_cast<uint32_t *>(word_at(A, n, 4 * n + 1)); }
+
+// waits until all `parts` workgroups of the matrix are counted in; false: the matrix is left.  A
+// bound of 0 leaves every matrix (each workgroup marks it before it counts itself in).
+JOLT_DEV bool gather_wait(uint32_t *word, int parts, int polls_max) {
+  for (int polls = 0;; ++polls) {
+    uint32_t w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (w & TRD_LEFT) return false;
+    if (w == (uint32_t)parts) return true;
+    // fails, and the loop goes on, if another workgroup counted itself in meanwhile
+    if (polls >= polls_max &&
+        __hip_atomic_compare_exchange_strong(word, &w, w | TRD_LEFT, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      return false;
+    __builtin_amdgcn_s_sleep(8);
+  }
 }
 
 JOLT_DEV void word_put(uint64_t *p, float v, uint32_t tag) {
@@ -99,17 +130,30 @@ JOLT_DEV float fold16(float a, float b) {
 // CC: columns per lane (n <= 64 CC); TW: waves per matrix; RW: rows per wave (n <= TW RW);
 // NW: waves per workgroup (TW / NW workgroups per matrix)
 template <int CC, int TW, int RW, int NW>
-__global__ void __launch_bounds__(NW * 64, 1) k_trd_reg(EigBatch b, int mat0, int spin_max) {
+__global__ void __launch_bounds__(NW * 64, 1) k_trd_reg(EigBatch b, int gather_max, int spin_max) {
   constexpr int P = TW / NW, RP = (RW + 3) / 4 * 4;
-  const int mat = mat0 + blockIdx.x / P, part = blockIdx.x % P, n = b.n;
+  const int tid = threadIdx.x, n = b.n;
+  int job = blockIdx.x;
+  __shared__ int head, give_up;          // head: the job drawn, then whether its matrix is left
+  if (tid == 0) give_up = 0;
+  if constexpr (P > 1) {
+    if (tid == 0) {
+      const int j = (int)__hip_atomic_fetch_add(ticket_word(b.A, n), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t *word = gather_word(b.A + (int64_t)(j / P) * b.mat_stride, n);
+      if (gather_max == 0) __hip_atomic_fetch_or(word, TRD_LEFT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      head = j;
+    }
+    __syncthreads();
+    job = __builtin_amdgcn_readfirstlane(head);
+  }
+  const int mat = job / P, part = job % P;
   float *A = b.A + (int64_t)mat * b.mat_stride;
   double *dd = b.d + (int64_t)mat * n, *ee = b.e + (int64_t)mat * n;
   float *tau = b.tau + (int64_t)mat * n;
-  const int tid = threadIdx.x, lane0 = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), rho = part * NW + wave;
+  const int lane0 = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), rho = part * NW + wave;
   int lane = lane0;
   __shared__ float ex[2][2][64 * CC];    // [parity][products, row i + 1][column]
-  __shared__ int give_up;
-  if (tid == 0) give_up = 0;
 
   // rows TW j + rho; entries past n are zero
   float a[RW][CC], x[CC];
@@ -127,7 +171,13 @@ __global__ void __launch_bounds__(NW * 64, 1) k_trd_reg(EigBatch b, int mat0, in
   }
 #pragma unroll
   for (int c = 0; c < CC; ++c) x[c] = 64 * c + lane < n ? A[(uint32_t)((64 * c + lane) * n)] : 0.f;
+  if constexpr (P > 1) {
+    __syncthreads();                     // every wave has read the job
+    if (tid == 0) head = gather_wait(gather_word(A, n), P, gather_max) ? 0 : 1;
+  }
   __syncthreads();
+  if constexpr (P > 1)
+    if (head) return;
 
   float vp[CC], wp[CC];                  // the previous column's update, pending at odd columns
 #pragma unroll
@@ -329,11 +379,11 @@ __global__ void __launch_bounds__(NW * 64, 1) k_trd_reg(EigBatch b, int mat0, in
   }
 }
 
-// before: the exchange words cleared; after: the upper triangle, the diagonal and the last
+// before: the exchange, gather and ticket words cleared; after: the upper triangle, the diagonal and the last
 // column zeroed (the dense V that the blocked back-transform multiplies by)
 __global__ void k_trd_words_clear(EigBatch b) {
   float *A = b.A + (int64_t)blockIdx.y * b.mat_stride;
-  for (int e = blockIdx.x * 256 + threadIdx.x; e < 4 * b.n; e += gridDim.x * 256)
+  for (int e = blockIdx.x * 256 + threadIdx.x; e < 4 * b.n + 2; e += gridDim.x * 256)
     __hip_atomic_store(word_at(A, b.n, e), (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __global__ void k_trd_clean(EigBatch b) {
@@ -344,13 +394,210 @@ __global__ void k_trd_clean(EigBatch b) {
       if (c >= r || c == n - 1) A[(int64_t)r * n + c] = 0.f;
 }
 
+// Tridiagonalisation in one workgroup per matrix, the matrix in global memory (L2), for n <= 1024:
+// what the register kernel leaves (left != 0: matrices marked in their gather word, of which only
+// the lower triangle is read).  Writes d, e, tau and leaves v_i in column i of A (rows i+1..n-1,
+// v_i(i+1) = 1) with zeros above, as the register kernel and the cleaning pass do.
+//
+// Blocked in panels of SB columns (the LAPACK latrd scheme inside one workgroup): the
+// panel's reflectors V and the vectors W (A_i v_i corrected for the panel's earlier
+// reflectors, then w += K v) are kept in LDS by absolute row.  Column i is brought up to
+// date with the panel's earlier reflectors only when it becomes current; the mat-vec reads
+// the trailing matrix as it was at the panel start and subtracts V (W^T v) + W (V^T v); the
+// trailing matrix past the panel takes the rank-2 SB update once, at the panel end.  Each
+// column then reads the trailing matrix once instead of three times (mat-vec, and the
+// read and write of an immediate rank-2 update).
+constexpr int SYTD2_THREADS = 1024;
+
+// Workgroup sum with one barrier: successive calls alternate between two halves of red
+// (2 x waves entries), so a call never overwrites values an earlier call is still reading.
+JOLT_DEV double block_sum1(double v, double *red, int &flip) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  v = wave_sum(v);
+  double *r = red + flip * nw;
+  flip ^= 1;
+  if (lane == 0) r[wave] = v;
+  __syncthreads();
+  double s = 0.0;
+  for (int w = 0; w < nw; ++w) s += r[w];
+  return s;
+}
+
+constexpr int SB = 16, SBL = SB + 1;     // panel width, LDS row stride of V and W
+
+size_t sytd2_lds_bytes(int n) { return ((size_t)2 * n + (size_t)2 * n * SBL + 2 * SB) * sizeof(float); }
+
+__global__ void __launch_bounds__(SYTD2_THREADS) k_sytd2(EigBatch b, int left) {
+  const int mat = blockIdx.x, n = b.n;
+  float *A = b.A + (int64_t)mat * b.mat_stride;
+  if (left && !(*gather_word(A, n) & TRD_LEFT)) return;
+  double *dd = b.d + (int64_t)mat * n, *ee = b.e + (int64_t)mat * n;
+  float *tau = b.tau + (int64_t)mat * n;
+  extern __shared__ float sh[];
+  float *v = sh, *w = sh + n;
+  float *Vp = w + n, *Wp = Vp + (size_t)n * SBL, *yv = Wp + (size_t)n * SBL;
+  __shared__ double red[2 * (SYTD2_THREADS / 64)];
+  __shared__ double s_alpha;                        // x[0] of the current column
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = SYTD2_THREADS / 64;
+  int flip = 0;
+  if (left) {
+    __syncthreads();                     // every thread has read the word
+    for (int r = wave; r < n; r += nw)
+      for (int c = lane; c < r; c += 64) A[(int64_t)c * n + r] = A[(int64_t)r * n + c];
+    __syncthreads();
+  }
+  for (int k0 = 0; k0 < n - 1; k0 += SB) {
+    const int jb = min(SB, n - 1 - k0);
+    for (int q = tid; q < (n - k0) * SBL; q += SYTD2_THREADS) {
+      Vp[(size_t)k0 * SBL + q] = 0.f;
+      Wp[(size_t)k0 * SBL + q] = 0.f;
+    }
+    __syncthreads();
+    for (int j = 0; j < jb; ++j) {
+      const int i = k0 + j, L = n - 1 - i;
+      // column i (rows i..n-1) brought up to date with reflectors k0 .. i-1; the squared
+      // norm of x[1..] is accumulated on the way
+      double part = 0.0;
+      for (int r = i + tid; r < n; r += SYTD2_THREADS) {
+        float a = A[(int64_t)r * n + i];
+        for (int p = 0; p < j; ++p)
+          a -= Vp[(size_t)r * SBL + p] * Wp[(size_t)i * SBL + p] + Wp[(size_t)r * SBL + p] * Vp[(size_t)i * SBL + p];
+        if (r == i) A[(int64_t)i * n + i] = a;
+        else v[r - i - 1] = a;
+        if (r == i + 1) s_alpha = a;
+        if (r > i + 1) part += (double)a * (double)a;
+      }
+      // its barrier also publishes v and x[0]; v[0] is overwritten below, so x[0] is read
+      // from its own copy (rewritten only after two more barriers)
+      const double sigma = block_sum1(part, red, flip);
+      const double alpha = s_alpha;
+      double beta, tv, scal;
+      if (sigma == 0.0) {
+        tv = 0.0; beta = alpha; scal = 0.0;
+      } else {
+        beta = -copysign(sqrt(alpha * alpha + sigma), alpha);
+        tv = (beta - alpha) / beta;
+        scal = 1.0 / (alpha - beta);
+      }
+      // v = x scaled (v[0] = 1); every entry has one owner in this loop
+      for (int r = i + 1 + tid; r < n; r += SYTD2_THREADS) {
+        const int t = r - i - 1;
+        float vt = (t == 0) ? 1.f : (float)((double)v[t] * scal);
+        if (tv == 0.0) vt = (t == 0) ? 1.f : 0.f;
+        v[t] = vt;
+        A[(int64_t)r * n + i] = vt;
+        Vp[(size_t)r * SBL + j] = vt;
+      }
+      if (tid == 0) { ee[i] = beta; tau[i] = (float)tv; }
+      __syncthreads();
+      if (tv == 0.0) continue;                     // W column stays zero
+      const float tf = (float)tv;
+      // w' = A22 v over the trailing matrix as of the panel start: a wavefront takes four
+      // rows at a time (rows r, r + nw, r + 2 nw, r + 3 nw) so that their loads are in
+      // flight together; rows past L read row L - 1 and are not stored
+      for (int r0 = wave; r0 < L; r0 += 4 * nw) {
+        const float *row[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) row[u] = A + (int64_t)(i + 1 + min(r0 + u * nw, L - 1)) * n + (i + 1);
+        float sacc[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int c = lane; c < L; c += 64) {
+          float x[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) x[u] = row[u][c];
+          const float vc = v[c];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) sacc[u] = fmaf(x[u], vc, sacc[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float su = wave_sum(sacc[u]);
+          if (lane == 0 && r0 + u * nw < L) w[r0 + u * nw] = su;
+        }
+      }
+      // yv = [W^T v ; V^T v] over rows i+1.. for the panel's earlier reflectors
+      for (int q = wave; q < 2 * j; q += nw) {
+        const float *col = (q < j ? Wp : Vp) + (q < j ? q : q - j);
+        float sacc = 0.f;
+        for (int t = lane; t < L; t += 64) sacc = fmaf(col[(size_t)(i + 1 + t) * SBL], v[t], sacc);
+        sacc = wave_sum(sacc);
+        if (lane == 0) yv[q < j ? q : SB + q - j] = sacc;
+      }
+      __syncthreads();
+      // corrected w = tau (w' - V yv_W - W yv_V), kept in a register by the thread that owns
+      // row t, and its dot with v for K
+      part = 0.0;
+      float wt[(1024 + SYTD2_THREADS - 1) / SYTD2_THREADS];
+#pragma unroll
+      for (int u = 0; u < (int)(sizeof(wt) / sizeof(float)); ++u) {
+        const int t = tid + u * SYTD2_THREADS;
+        wt[u] = 0.f;
+        if (t < L) {
+          float c = w[t];
+          const size_t rr = (size_t)(i + 1 + t) * SBL;
+          for (int p = 0; p < j; ++p) c -= Vp[rr + p] * yv[p] + Wp[rr + p] * yv[SB + p];
+          wt[u] = tf * c;
+          part += (double)wt[u] * (double)v[t];
+        }
+      }
+      const float K = (float)(-0.5 * tv * block_sum1(part, red, flip));
+#pragma unroll
+      for (int u = 0; u < (int)(sizeof(wt) / sizeof(float)); ++u) {
+        const int t = tid + u * SYTD2_THREADS;
+        if (t < L) Wp[(size_t)(i + 1 + t) * SBL + j] = fmaf(K, v[t], wt[u]);
+      }
+      __syncthreads();
+    }
+    // trailing matrix past the panel: A -= V W^T + W V^T (both triangles)
+    const int s0 = k0 + jb;
+    for (int r = s0 + wave; r < n; r += nw) {
+      float vr[SB], wr[SB];
+#pragma unroll
+      for (int p = 0; p < SB; ++p) { vr[p] = Vp[(size_t)r * SBL + p]; wr[p] = Wp[(size_t)r * SBL + p]; }
+      float *row = A + (int64_t)r * n;
+      for (int c = s0 + lane; c < n; c += 64) {
+        float acc = 0.f;
+#pragma unroll
+        for (int p = 0; p < SB; ++p) acc = fmaf(vr[p], Wp[(size_t)c * SBL + p], fmaf(wr[p], Vp[(size_t)c * SBL + p], acc));
+        row[c] -= acc;
+      }
+    }
+    __syncthreads();
+  }
+  // diagonal of T, then zero the strictly upper part and diagonal of the reflector block
+  for (int i = tid; i < n; i += SYTD2_THREADS) dd[i] = A[(int64_t)i * n + i];
+  if (tid == 0) { ee[n - 1] = 0.0; tau[n - 1] = 0.f; }
+  __syncthreads();
+  for (int r = wave; r < n; r += nw) {
+    float *row = A + (int64_t)r * n;
+    for (int c = lane; c < n; c += 64)
+      if (c >= r || c == n - 1) row[c] = 0.f;
+  }
+  if (n == 1 && tid == 0) A[0] = 0.f;
+}
+
+hipError_t launch_sytd2(const EigBatch &b, int left, hipStream_t st) {
+  if (b.n > SYTD2_THREADS) return hipErrorInvalidValue;   // one corrected w entry per thread
+  const size_t shm = sytd2_lds_bytes(b.n);
+  if (shm > 65536) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sytd2),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k_sytd2, dim3(b.n_mat), dim3(SYTD2_THREADS), shm, st, b, left);
+  return hipGetLastError();
+}
+
 template <int CC, int TW, int RW, int NW>
-hipError_t launch_reg(const EigBatch &b, int spin_max, hipStream_t st) {
+hipError_t launch_reg(const EigBatch &b, int gather_max, int spin_max, hipStream_t st) {
   static_assert(TW % NW == 0 && (TW / NW == 1 || TW >= 64), "waves per matrix");
   constexpr int P = TW / NW;
   if (b.n > 64 * CC || b.n > TW * RW) return hipErrorInvalidValue;
-  if (P > 1) hipLaunchKernelGGL(k_trd_words_clear, dim3((4 * b.n + 255) / 256, b.n_mat), dim3(256), 0, st, b);
-  hipLaunchKernelGGL((k_trd_reg<CC, TW, RW, NW>), dim3(b.n_mat * P), dim3(NW * 64), 0, st, b, 0, spin_max);
+  if (P > 1) hipLaunchKernelGGL(k_trd_words_clear, dim3((4 * b.n + 257) / 256, b.n_mat), dim3(256), 0, st, b);
+  hipLaunchKernelGGL((k_trd_reg<CC, TW, RW, NW>), dim3(b.n_mat * P), dim3(NW * 64), 0, st, b, gather_max, spin_max);
+  if (P > 1) {
+    const hipError_t e = launch_sytd2(b, 1, st);
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(k_trd_clean, dim3(std::min(b.n, 256), b.n_mat), dim3(256), 0, st, b);
   return hipGetLastError();
 }
@@ -359,15 +606,15 @@ hipError_t launch_reg(const EigBatch &b, int spin_max, hipStream_t st) {
 
 int trd_reg_workgroups(int n) { return n <= 256 ? 1 : n <= 576 ? 8 : n <= 768 ? 16 : 32; }
 
-hipError_t launch_trd_reg(const EigBatch &b, int spin_max, hipStream_t st) {
-  const int n = b.n, spin = std::max(spin_max, 0);
+hipError_t launch_trd_reg(const EigBatch &b, int gather_max, int spin_max, hipStream_t st) {
+  const int n = b.n, spin = std::max(spin_max, 0), gather = std::max(gather_max, 0);
   if (n < 1 || n > TRD_REG_MAX) return hipErrorInvalidValue;
   // up to n = 256 one workgroup (an exchange between workgroups costs what its compute does)
-  if (n <= 64) return launch_reg<1, 8, 8, 8>(b, spin, st);
-  if (n <= 128) return launch_reg<2, 8, 16, 8>(b, spin, st);
-  if (n <= 256) return launch_reg<4, 16, 16, 16>(b, spin, st);
-  if (n <= 384) return launch_reg<6, 64, 6, 8>(b, spin, st);
-  if (n <= 576) return launch_reg<9, 64, 9, 8>(b, spin, st);
-  if (n <= 768) return launch_reg<12, 128, 6, 8>(b, spin, st);
-  return launch_reg<16, 256, 4, 8>(b, spin, st);
+  if (n <= 64) return launch_reg<1, 8, 8, 8>(b, gather, spin, st);
+  if (n <= 128) return launch_reg<2, 8, 16, 8>(b, gather, spin, st);
+  if (n <= 256) return launch_reg<4, 16, 16, 16>(b, gather, spin, st);
+  if (n <= 384) return launch_reg<6, 64, 6, 8>(b, gather, spin, st);
+  if (n <= 576) return launch_reg<9, 64, 9, 8>(b, gather, spin, st);
+  if (n <= 768) return launch_reg<12, 128, 6, 8>(b, gather, spin, st);
+  return launch_reg<16, 256, 4, 8>(b, gather, spin, st);
 }

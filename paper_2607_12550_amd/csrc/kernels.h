@@ -244,12 +244,14 @@ struct EigBatch {
   int32_t pad_;
 };
 inline __host__ __device__ int refl_off(const EigBatch &b) { return b.refl_off > 0 ? b.refl_off : 1; }
-// Householder tridiagonalisation (lower): small n in one workgroup per matrix.
-// register-resident tridiagonalisation (n <= TRD_REG_MAX); spin_max bounds its waits, a matrix
-// that gave up has e[n-1] = NaN (0 otherwise)
+// Householder tridiagonalisation (lower) for n <= TRD_REG_MAX, the matrices in registers.
+// gather_max bounds the polls (about 1 us each) for all workgroups of a matrix to be running, past
+// which one workgroup reduces it from memory; spin_max bounds the exchange's waits, a matrix that
+// gave up there has e[n-1] = NaN (0 otherwise)
 constexpr int TRD_REG_MAX = 1024;
+constexpr int TRD_GATHER_DEFAULT = 1 << 16;
 int trd_reg_workgroups(int n);       // workgroups per matrix
-hipError_t launch_trd_reg(const EigBatch &b, int spin_max, hipStream_t st);
+hipError_t launch_trd_reg(const EigBatch &b, int gather_max, int spin_max, hipStream_t st);
 // Blocked multi-workgroup tridiagonalisation for large n (panels of nb columns).
 // work: sytrd_large_work_floats() device floats; tables: sytrd_large_table_entries().
 struct SytrdArgs {

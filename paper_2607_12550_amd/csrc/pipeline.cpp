@@ -315,7 +315,7 @@ int eig_values(Run &R, EigWs &e) {
   } else {
     e.b.refl_off = 1;
     StageTimer t(R.ctx, R.st, JOLT_STAGE_TRIDIAG_SMALL);
-    HIP_OK(launch_trd_reg(e.b, c->bulge_spin, R.st));
+    HIP_OK(launch_trd_reg(e.b, c->trd_gather, c->bulge_spin, R.st));
   }
   StageTimer t(R.ctx, R.st, JOLT_STAGE_EIGVALS);
   HIP_OK(launch_tridiag_eigvals(e.b, R.st));
@@ -1443,7 +1443,7 @@ extern "C" int jolt_slice_spectrum(jolt_ctx *ctx, const jolt_cell_desc *desc, in
   }
   {
     StageTimer t(ctx, st, JOLT_STAGE_TRIDIAG_SMALL);
-    HIP_OK(launch_trd_reg(e.b, ctx->bulge_spin, st));
+    HIP_OK(launch_trd_reg(e.b, ctx->trd_gather, ctx->bulge_spin, st));
   }
   {
     StageTimer t(ctx, st, JOLT_STAGE_EIGVALS);
@@ -1653,6 +1653,12 @@ extern "C" int jolt_debug_set(jolt_ctx *ctx, int what, int64_t value) {
     if (value < 0 || value > SB_SPIN_DEFAULT)
       return jolt_fail(JOLT_E_INVAL, "jolt_debug_set: bulge-chase wait bound must be in 0..%d", SB_SPIN_DEFAULT);
     ctx->bulge_spin = (int)value;
+    return JOLT_OK;
+  }
+  if (what == JOLT_DBG_TRD_GATHER) {
+    if (value < 0 || value > SB_SPIN_DEFAULT)
+      return jolt_fail(JOLT_E_INVAL, "jolt_debug_set: gather bound must be in 0..%d", SB_SPIN_DEFAULT);
+    ctx->trd_gather = (int)value;
     return JOLT_OK;
   }
   if (what == JOLT_DBG_TRD_TWO_STAGE) {
