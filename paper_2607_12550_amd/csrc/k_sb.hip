@@ -727,6 +727,7 @@ __global__ void __launch_bounds__(256) k_sb_bulge_finish(SbArgs a, int mat0) {
   const int n = a.n;
   const SbView M = sview(a, mat0 + blockIdx.x);
   const bool bad = bulge_words(M)[1] != 0;
+  if (threadIdx.x == 0) a.gave_up[mat0 + blockIdx.x] = bad;
   for (int i = threadIdx.x; i < n; i += 256) {
     M.d[i] = bad ? __builtin_nan("") : (double)M.AB[(int64_t)i * SBW];
     M.e[i] = (i + 1 < n) ? (double)M.AB[(int64_t)i * SBW + 1] : 0.0;
@@ -1060,6 +1061,7 @@ hipError_t launch_sb_reduce(const EigBatch &b, float *work, const GemmProblem *t
   a.e = b.e;
   a.tau = b.tau;
   a.spin_max = spin_max < 0 ? 0 : spin_max;
+  a.gave_up = b.gave_up;
   const int panels = (n + SB - 1) / SB;
   for (int p = 0; p < panels; ++p) {
     const int m = n - (p * SB + SB);

@@ -37,8 +37,7 @@
 // launches could hold one XCD each with workgroups that waited for the other's; drawing them costs
 // 0.2 of 6.9 ms at n = 1001, 0.2 of 4.6 ms for 16 matrices of order 700, nothing up to 576: the
 // parts of a matrix are then spread less evenly over the XCDs.)  A second bound (spin_max) ends the exchange's own
-// waits; a workgroup that gives up there leaves e[n-1] = NaN (otherwise 0), which the caller
-// reports.
+// waits; a workgroup that gives up there marks its matrix in b.gave_up, which the caller reports.
 // Whole spectrum of 4 cells, one workgroup per matrix with blocked updates -> this: T = 256 4.1 ->
 // 2.5 ms, 522 10.7 -> 5.0 ms, 700 18.1 -> 6.9 ms; against the one-stage reduction of larger
 // matrices T = 1001 21.1 -> 10.0 ms.  At n = 1300 the wave's registers spill and it loses (36 ms to
@@ -367,7 +366,7 @@ __global__ void __launch_bounds__(NW * 64, 1) k_trd_reg(EigBatch b, int gather_m
     for (int c = 0; c < CC; ++c) { vp[c] = 0.f; wp[c] = 0.f; }
   }
   if (dead) {
-    if (tid == 0) ee[n - 1] = __builtin_nan("");
+    if (tid == 0) b.gave_up[mat] = 1;
     return;
   }
   if (rho == (n - 1) % TW) {
@@ -383,6 +382,7 @@ __global__ void __launch_bounds__(NW * 64, 1) k_trd_reg(EigBatch b, int gather_m
 // column zeroed (the dense V that the blocked back-transform multiplies by)
 __global__ void k_trd_words_clear(EigBatch b) {
   float *A = b.A + (int64_t)blockIdx.y * b.mat_stride;
+  if (blockIdx.x == 0 && threadIdx.x == 0) b.gave_up[blockIdx.y] = 0;
   for (int e = blockIdx.x * 256 + threadIdx.x; e < 4 * b.n + 2; e += gridDim.x * 256)
     __hip_atomic_store(word_at(A, b.n, e), (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -240,14 +240,16 @@ struct EigBatch {
   double *d, *e;         // tridiagonal [n_mat][n]
   float *tau;            // [n_mat][n]
   double *lam;           // eigenvalues, descending [n_mat][n]
+  int32_t *gave_up;      // [n_mat]: 1 if the reduction did not complete (written by the reductions
+                         // that wait between workgroups: in registers and two-stage)
   int32_t refl_off;      // row of reflector i's unit is i + refl_off (0 read as 1: one-stage)
   int32_t pad_;
 };
 inline __host__ __device__ int refl_off(const EigBatch &b) { return b.refl_off > 0 ? b.refl_off : 1; }
 // Householder tridiagonalisation (lower) for n <= TRD_REG_MAX, the matrices in registers.
 // gather_max bounds the polls (about 1 us each) for all workgroups of a matrix to be running, past
-// which one workgroup reduces it from memory; spin_max bounds the exchange's waits, a matrix that
-// gave up there has e[n-1] = NaN (0 otherwise)
+// which one workgroup reduces it from memory; spin_max bounds the exchange's waits (b.gave_up, for
+// matrices of more than one workgroup)
 constexpr int TRD_REG_MAX = 1024;
 constexpr int TRD_GATHER_DEFAULT = 1 << 16;
 int trd_reg_workgroups(int n);       // workgroups per matrix
@@ -313,6 +315,7 @@ struct SbArgs {
   int32_t n;
   int32_t spin_max;      // bound of one dependency wait of the bulge chase (0: the first wait
                          // gives up); a chase that gives up leaves NaN on the diagonal
+  int32_t *gave_up;
   float *work;
   int64_t work_stride;
   double *d, *e;

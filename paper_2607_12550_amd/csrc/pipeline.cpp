@@ -38,6 +38,7 @@ struct EigWs {
   double *Z = nullptr, *lu = nullptr;
   int32_t *k = nullptr;
   int32_t *status = nullptr;   // inverse-iteration convergence flags, one per matrix
+  bool flagged = false;        // this call's reduction wrote b.gave_up
   float *bt = nullptr;
   float *trd = nullptr;    // blocked tridiagonalisation work (large n only)
   int kmax = 0;
@@ -98,6 +99,7 @@ void carve_eig(Carver &cv, EigWs &e, int nmat, int n, int kmax, float *A) {
   e.kmax = kmax;
   e.k = cv.take<int32_t>(nmat);
   e.status = cv.take<int32_t>(nmat);
+  e.b.gave_up = cv.take<int32_t>(nmat);
   if (n > SYTRD_SMALL_MAX)
     e.trd = cv.take<float>(std::max(sytrd_large_work_floats(nmat, n, SYTRD_NB), sb_work_floats(nmat, n)));
   if (kmax > 0) {
@@ -258,6 +260,7 @@ int eig_values(Run &R, EigWs &e) {
     const bool two = c->trd_two_stage == 1 ||
                      (c->trd_two_stage < 0 && (int64_t)e.b.n_mat * e.b.n >= kTwoStageMinWork);
     e.b.refl_off = two ? sb_band() : 1;
+    e.flagged = two;
     const size_t nt = two ? sb_table_entries(e.b.n_mat, e.b.n) : sytrd_large_table_entries(e.b.n_mat, e.b.n, SYTRD_NB);
     GemmProblem *tab = R.tab_slice(nt);
     if (!tab) return jolt_fail(JOLT_E_WORKSPACE, "GEMM problem table overflow");
@@ -270,7 +273,7 @@ int eig_values(Run &R, EigWs &e) {
       // group of matrices, and replay the groups side by side, the first on the caller's
       // stream and the others on private streams between a fork from and a join into it
       // (timed as one stage when profiling is on; its kernels are told apart by a kernel trace)
-      std::vector<const void *> key{e.b.A, e.trd, tab, e.b.d, e.b.e, e.b.tau,
+      std::vector<const void *> key{e.b.A, e.trd, tab, e.b.d, e.b.e, e.b.tau, e.b.gave_up,
                                     reinterpret_cast<const void *>((intptr_t)e.b.n),
                                     reinterpret_cast<const void *>((intptr_t)e.b.n_mat),
                                     reinterpret_cast<const void *>((intptr_t)(two ? 2 : 1)),
@@ -314,6 +317,7 @@ int eig_values(Run &R, EigWs &e) {
     }
   } else {
     e.b.refl_off = 1;
+    e.flagged = trd_reg_workgroups(e.b.n) > 1;
     StageTimer t(R.ctx, R.st, JOLT_STAGE_TRIDIAG_SMALL);
     HIP_OK(launch_trd_reg(e.b, c->trd_gather, c->bulge_spin, R.st));
   }
@@ -355,8 +359,8 @@ int eig_vectors(Run &R, EigWs &e, const std::vector<int> &k, float *U, int64_t l
 struct CallChecks {
   int nc = 0, n_orth = 0;
   bool spectrum = false;
-  std::vector<int32_t> bad, clamp, tstat, fstat;
-  std::vector<double> E, d0;   // d0: a tridiagonal's entry that is NaN if its reduction gave up
+  std::vector<int32_t> bad, clamp, gave_up, tstat, fstat;
+  std::vector<double> E;
 
   int queue(Run &R, int nc_, bool spectrum_computed, bool token_vecs, bool feature_vecs) {
     nc = nc_;
@@ -367,17 +371,11 @@ struct CallChecks {
       HIP_OK(hipMemcpyAsync(bad.data(), R.w.nonfinite, nc * sizeof(int32_t), hipMemcpyDeviceToHost, R.st));
       HIP_OK(hipMemcpyAsync(E.data(), R.w.E, nc * sizeof(double), hipMemcpyDeviceToHost, R.st));
       n_orth = R.orth_calls;
-      // a bulge chase that gave up leaves NaN on its diagonal
-      const EigBatch &tb = R.w.teig.b;
-      if (tb.d && tb.refl_off == sb_band()) {
-        d0.resize(tb.n_mat);
-        HIP_OK(hipMemcpy2DAsync(d0.data(), sizeof(double), tb.d, (size_t)tb.n * sizeof(double), sizeof(double),
-                                tb.n_mat, hipMemcpyDeviceToHost, R.st));
-      } else if (tb.d && trd_reg_workgroups(tb.n) > 1) {
-        // and a register-resident reduction that gave up NaN as its (unused) last off-diagonal
-        d0.resize(tb.n_mat);
-        HIP_OK(hipMemcpy2DAsync(d0.data(), sizeof(double), tb.e + tb.n - 1, (size_t)tb.n * sizeof(double),
-                                sizeof(double), tb.n_mat, hipMemcpyDeviceToHost, R.st));
+      // one contiguous word per matrix: a strided copy to the host takes 5 us a row
+      if (R.w.teig.flagged) {
+        gave_up.resize(R.w.teig.b.n_mat);
+        HIP_OK(hipMemcpyAsync(gave_up.data(), R.w.teig.b.gave_up, gave_up.size() * sizeof(int32_t),
+                              hipMemcpyDeviceToHost, R.st));
       }
       if (n_orth) {
         clamp.resize((size_t)n_orth * 2 * nc);
@@ -410,8 +408,8 @@ struct CallChecks {
                                           "pass (%d pivots clamped in the second)", c, o, second);
       }
     }
-    for (int c = 0; c < (int)d0.size(); ++c)
-      if (!std::isfinite(d0[c]))
+    for (int c = 0; c < (int)gave_up.size(); ++c)
+      if (gave_up[c])
         return jolt_fail(JOLT_E_NOCONV, "cell %d: the tridiagonal reduction of the token Gram did not complete", c);
     for (int c = 0; c < (int)tstat.size(); ++c)
       if (tstat[c]) return jolt_fail(JOLT_E_NOCONV, "cell %d: token-mode inverse iteration did not converge", c);
@@ -1449,13 +1447,14 @@ extern "C" int jolt_slice_spectrum(jolt_ctx *ctx, const jolt_cell_desc *desc, in
     StageTimer t(ctx, st, JOLT_STAGE_EIGVALS);
     HIP_OK(launch_tridiag_eigvals(e.b, st));
   }
-  std::vector<double> lam((size_t)n_cells * m), last(n_cells);
-  HIP_OK(hipMemcpy2DAsync(last.data(), sizeof(double), e.b.e + m - 1, (size_t)m * sizeof(double), sizeof(double),
-                          n_cells, hipMemcpyDeviceToHost, st));
+  std::vector<double> lam((size_t)n_cells * m);
+  std::vector<int32_t> gave_up(n_cells, 0);
+  if (trd_reg_workgroups(m) > 1)
+    HIP_OK(hipMemcpyAsync(gave_up.data(), e.b.gave_up, n_cells * sizeof(int32_t), hipMemcpyDeviceToHost, st));
   HIP_OK(hipMemcpyAsync(lam.data(), e.b.lam, lam.size() * sizeof(double), hipMemcpyDeviceToHost, st));
   HIP_OK(hipStreamSynchronize(st));
   for (int c = 0; c < n_cells; ++c)
-    if (!std::isfinite(last[c]))
+    if (gave_up[c])
       return jolt_fail(JOLT_E_NOCONV, "cell %d: the tridiagonal reduction of the slice Gram did not complete", c);
   // eigenvalues are clipped at 0 (the Gram is positive semi-definite)
   for (size_t i = 0; i < lam.size(); ++i) lam_s[i] = std::max(0.0, lam[i]);
