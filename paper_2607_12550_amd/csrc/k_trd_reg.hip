@@ -395,9 +395,10 @@ __global__ void k_trd_clean(EigBatch b) {
 }
 
 // Tridiagonalisation in one workgroup per matrix, the matrix in global memory (L2), for n <= 1024:
-// what the register kernel leaves (left != 0: matrices marked in their gather word, of which only
-// the lower triangle is read).  Writes d, e, tau and leaves v_i in column i of A (rows i+1..n-1,
-// v_i(i+1) = 1) with zeros above, as the register kernel and the cleaning pass do.
+// large batches (both triangles of the input read), and what the register kernel leaves (left != 0:
+// matrices marked in their gather word, of which only the lower triangle is read).  Writes d, e,
+// tau and leaves v_i in column i of A (rows i+1..n-1, v_i(i+1) = 1) with zeros above, as the
+// register kernel and the cleaning pass do.
 //
 // Blocked in panels of SB columns (the LAPACK latrd scheme inside one workgroup): the
 // panel's reflectors V and the vectors W (A_i v_i corrected for the panel's earlier
@@ -431,6 +432,7 @@ __global__ void __launch_bounds__(SYTD2_THREADS) k_sytd2(EigBatch b, int left) {
   const int mat = blockIdx.x, n = b.n;
   float *A = b.A + (int64_t)mat * b.mat_stride;
   if (left && !(*gather_word(A, n) & TRD_LEFT)) return;
+  if (!left && threadIdx.x == 0) b.gave_up[mat] = 0;
   double *dd = b.d + (int64_t)mat * n, *ee = b.e + (int64_t)mat * n;
   float *tau = b.tau + (int64_t)mat * n;
   extern __shared__ float sh[];
@@ -613,6 +615,14 @@ hipError_t launch_trd_reg(const EigBatch &b, int gather_max, int spin_max, hipSt
   if (n <= 64) return launch_reg<1, 8, 8, 8>(b, gather, spin, st);
   if (n <= 128) return launch_reg<2, 8, 16, 8>(b, gather, spin, st);
   if (n <= 256) return launch_reg<4, 16, 16, 16>(b, gather, spin, st);
+  // A round is the workgroups that run at once (two a CU up to n = 384, else one).  Batches of more
+  // rounds than n / 160 go to one workgroup per matrix, which takes 256 matrices a round; whole
+  // spectrum in registers to one workgroup each, ms (at the line's two sides):
+  //   n = 257: 64 matrices (1 round) 2.6 to 3.6, 96 (2) 3.9 to 3.8; 384: 128 (2) 6.1 to 7.2, 160 (3) 8.4 to 7.9;
+  //   n = 385: 64 (2) 5.7 to 6.6, 96 (3) 8.0 to 7.1; 522: 96 (3) 11.4 to 13.7, 128 (4) 14.5 to 13.9;
+  //   n = 577: 48 (3) 13.1 to 14.9, 64 (4) 16.8 to 15.5; 768: 64 (4) 22.2 to 30.0, 96 (6) 33.6 to 32.1
+  const int64_t round = n <= 384 ? 512 : 256;
+  if (n <= 768 && ((int64_t)b.n_mat * trd_reg_workgroups(n) + round - 1) / round > n / 160) return launch_sytd2(b, 0, st);
   if (n <= 384) return launch_reg<6, 64, 6, 8>(b, gather, spin, st);
   if (n <= 576) return launch_reg<9, 64, 9, 8>(b, gather, spin, st);
   if (n <= 768) return launch_reg<12, 128, 6, 8>(b, gather, spin, st);

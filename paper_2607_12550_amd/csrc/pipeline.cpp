@@ -239,8 +239,9 @@ struct Run {
   }
 };
 
-// Matrices up to order 768 are tridiagonalised in registers, larger ones too unless a
-// reduction was asked for by name, as long as the whole batch fits the chip at once.
+// Matrices up to order 768 are tridiagonalised in registers (launch_trd_reg gives large batches to
+// one workgroup per matrix), larger ones too unless a reduction was asked for by name, as long as
+// the whole batch fits the chip at once.
 bool trd_in_registers(const jolt_ctx *c, const EigBatch &b) {
   if (b.n <= SYTRD_SMALL_MAX) return true;
   return c->trd_two_stage < 0 && b.n <= TRD_REG_MAX && (int64_t)b.n_mat * trd_reg_workgroups(b.n) <= 256;

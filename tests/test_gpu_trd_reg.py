@@ -50,6 +50,24 @@ def test_spectrum_and_factor(T):
         assert np.abs(U.T @ U - np.eye(r)).max() <= 1e-5
 
 
+# batches in registers of more workgroups than the chip holds at once (512, 320), and batches of
+# more rounds than stay there, which go to one workgroup per matrix
+@pytest.mark.parametrize("T, n", [(450, 64), (700, 20), (300, 72), (577, 50)])
+def test_batches_larger_than_the_chip(T, n):
+    """Spectra spread over batches of several rounds of workgroups, every matrix a differently
+    scaled copy of one of two, match the oracle's (a mix-up between matrices would show)."""
+    base = _cells(T, 2)
+    lam0 = [np.linalg.eigvalsh(_gram(x.astype(np.float32).astype(np.float64)))[::-1] for x in base]
+    scale = [1.0 + i / 64.0 for i in range(n)]
+    xs, ex, desc = device_cells([base[i % 2] * scale[i] for i in range(n)], "f32")
+    note("jolt_spectrum T", T, "cells", n)
+    lam = np.array(J.jolt_spectrum(ctx(), desc, xs, None, None, workspace(desc, n))[1])
+    for i in range(n):
+        # 1e-6 for the reduction and 2^-23 for the rounding of the scaled copies
+        want = lam0[i % 2] * scale[i] ** 2
+        assert np.abs(lam[i][:T] - np.maximum(want, 0)).max() <= 1.2e-6 * want[0], i
+
+
 def test_exchange_that_gives_up_is_reported():
     """A wait bound of zero (JOLT_DBG_BULGE_SPIN, forced from the host) ends the exchange between
     workgroups at its first unanswered poll; every wave still ends normally and the call reports
