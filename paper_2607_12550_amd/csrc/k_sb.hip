@@ -40,7 +40,7 @@ constexpr int SBW = 2 * SB;       // band-buffer entries per column (band and bu
 constexpr int PQ_NT = 1024;       // panel QR: threads per matrix
 constexpr int SY_ROWS = 128;      // rows of X per workgroup of the symmetric product
 constexpr int SY_NT = 256;
-constexpr int BG_WAVES = 4;       // bulge chase: wavefronts per workgroup, one per SIMD
+constexpr int BG_WAVES = 8;       // bulge chase: wavefronts per workgroup, two per SIMD
 constexpr int BG_DONE = 1 << 20;  // progress word of a finished sweep (above any step count)
 constexpr int BT_BLOCK = 128;     // reflectors per block of the stage-1 back-transform
 
@@ -515,7 +515,7 @@ __global__ void __launch_bounds__(SY_NT) k_sb_zform(SbArgs a, int p, int mat0) {
 // and progress words are relaxed agent-scope atomics (coherent across the XCDs); a step's stores
 // have completed (vmcnt) before its progress word is written, at the start of the next step, when
 // the wave has waited for its loads anyway.  Eight matrices of order 4096 per launch: 157 ms with
-// one workgroup each -> 86 ms with eight.
+// one workgroup of eight waves each -> 86 ms with 32 waves.
 JOLT_DEV float band_ld(const float *base, uint32_t idx) {
   return __uint_as_float(__hip_atomic_load(reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(base) + 4u * idx),
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
@@ -1073,8 +1073,13 @@ hipError_t launch_sb_reduce(const EigBatch &b, float *work, const GemmProblem *t
     hipError_t e = launch_update3(tab_dev + (size_t)p * b.n_mat + m0, nm, m, st);
     if (e != hipSuccess) return e;
   }
-  // enough wavefronts for the sweeps that can be in flight
-  const int groups = std::max(1, std::min(8, (n + 511) / 512));
+  // Enough wavefronts for the sweeps that can be in flight, on few CUs: a chase's waves hold over
+  // 200 registers each until its end, and a CU that holds one takes no panel workgroup (four
+  // waves per SIMD of 104).  With workgroups of four waves two groups of matrices in their chase
+  // could hold all 256 CUs while another still had panels to factor: 64 matrices of order 4096 took
+  // 253 or 331 ms a spectrum, at random.  Eight waves on at most 64 CUs per group: 245 to 256 (128
+  // matrices 458 or 537 to 396 ms, 240 of order 1100 68 to 46).
+  const int groups = std::max(1, std::min({4, (n + 1199) / 1200, 64 / nm}));
   hipLaunchKernelGGL(k_sb_bulge_clear, dim3(nm), dim3(256), 0, st, a, m0);
   hipLaunchKernelGGL(k_sb_bulge, dim3(nm * groups), dim3(BG_WAVES * 64), 0, st, a, m0, groups);
   hipLaunchKernelGGL(k_sb_bulge_finish, dim3(nm), dim3(256), 0, st, a, m0);

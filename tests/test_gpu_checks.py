@@ -279,3 +279,31 @@ def test_bulge_chase_that_gives_up_is_reported():
                 J.jolt_debug_set(c2, J.JOLT_DBG_BULGE_SPIN, bad)
     finally:
         J.jolt_destroy(c2)
+
+
+@pytest.mark.parametrize("T", [1201, 2500])
+def test_bulge_chase_over_several_workgroups(T):
+    """Orders whose sweeps are shared by two and by three workgroups per matrix (JOLT_DBG_TRD_TWO_STAGE
+    = 1): spectra of three fp32 cells within 1e-5 of lambda_1, and the same bits on one stream and
+    on three (JOLT_DBG_TRD_LANES)."""
+    rng = np.random.default_rng(T)
+    cells = [rng.standard_normal((2, T, 8)) @ rng.standard_normal((8, 64)) + 0.3 * rng.standard_normal((2, T, 64)) for _ in range(3)]
+    xs, ex, desc = device_cells(cells, "f32")
+    ws = workspace(desc, 3)
+    c2 = J.jolt_create(0)
+    try:
+        J.jolt_debug_set(c2, J.JOLT_DBG_TRD_TWO_STAGE, 1)
+        out = []
+        for lanes in (4, 1):
+            J.jolt_debug_set(c2, J.JOLT_DBG_TRD_LANES, lanes)
+            note("two-stage spectrum T", T, "lanes", lanes)
+            out.append(np.array(J.jolt_spectrum(c2, desc, xs, None, None, ws)[1]))
+    finally:
+        J.jolt_destroy(c2)
+    assert np.array_equal(out[0], out[1])
+    for c in range(3):
+        # the Gram's spectrum from its small side, zeros past the rank
+        X2 = ex[c].transpose(1, 0, 2).reshape(T, -1)
+        want = np.zeros(T)
+        want[:128] = np.linalg.eigvalsh(X2.T @ X2)[::-1]
+        assert np.abs(out[0][c][:T] - np.maximum(want, 0)).max() <= 1e-5 * want[0]
