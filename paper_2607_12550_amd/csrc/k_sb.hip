@@ -516,13 +516,17 @@ __global__ void __launch_bounds__(SY_NT) k_sb_zform(SbArgs a, int p, int mat0) {
 // have completed (vmcnt) before its progress word is written, at the start of the next step, when
 // the wave has waited for its loads anyway.  Eight matrices of order 4096 per launch: 157 ms with
 // one workgroup of eight waves each -> 86 ms with 32 waves.
+// With one workgroup per matrix they stay in its CU (workgroup scope): whole spectrum of 120 matrices
+// of order 1100 36.6 -> 35.9 ms, of 256 of order 2048 150.7 -> 146.0 (before the chase was shared: 35.9, 149.4).
+template <int SCOPE>
 JOLT_DEV float band_ld(const float *base, uint32_t idx) {
   return __uint_as_float(__hip_atomic_load(reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(base) + 4u * idx),
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                                           __ATOMIC_RELAXED, SCOPE));
 }
+template <int SCOPE>
 JOLT_DEV void band_st(float *base, uint32_t idx, float v) {
   __hip_atomic_store(reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(base) + 4u * idx), __float_as_uint(v),
-                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                     __ATOMIC_RELAXED, SCOPE);
 }
 JOLT_DEV int word_ld(const int *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 JOLT_DEV void word_st(int *p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -536,6 +540,7 @@ __global__ void __launch_bounds__(256) k_sb_bulge_clear(SbArgs a, int mat0) {
   for (int i = threadIdx.x; i < a.n + 64; i += 256) word_st(w + i, 0);
 }
 
+template <int SCOPE>
 __global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0, int groups) {
   const int mat = mat0 + blockIdx.x / groups, n = a.n;
   const SbView M = sview(a, mat);
@@ -555,8 +560,8 @@ __global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0, 
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const int c = 16 * h + q;
-      E[q] = (lj < ne && c < ln) ? band_ld(AB, (uint32_t)((r0 + c) * SBW + (ln + lj - c))) : 0.f;
-      D[q] = (c + lj < ln) ? band_ld(AB, (uint32_t)((r0 + c) * SBW + lj)) : 0.f;
+      E[q] = (lj < ne && c < ln) ? band_ld<SCOPE>(AB, (uint32_t)((r0 + c) * SBW + (ln + lj - c))) : 0.f;
+      D[q] = (c + lj < ln) ? band_ld<SCOPE>(AB, (uint32_t)((r0 + c) * SBW + lj)) : 0.f;
     }
   };
   while (true) {
@@ -598,7 +603,7 @@ __global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0, 
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
           const int i = 16 * h + q;
-          L[q] = (lj == 0 && i < ln) ? band_ld(AB, (uint32_t)(s * SBW + 1 + i)) : 0.f;
+          L[q] = (lj == 0 && i < ln) ? band_ld<SCOPE>(AB, (uint32_t)(s * SBW + 1 + i)) : 0.f;
         }
       } else {
 #pragma unroll
@@ -645,7 +650,7 @@ __global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0, 
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
               const int i = 16 * h + q;
-              if (i < ln) band_st(AB, (uint32_t)(s * SBW + 1 + i), L[q]);
+              if (i < ln) band_st<SCOPE>(AB, (uint32_t)(s * SBW + 1 + i), L[q]);
             }
           }
         }
@@ -661,7 +666,7 @@ __global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0, 
 #pragma unroll
           for (int q = 0; q < 16; ++q) {
             const int c = 16 * h + q;
-            band_st(AB, (uint32_t)((c0 + c) * SBW + (SB + lj - c)), tbw[lj * (SB + 1) + c]);
+            band_st<SCOPE>(AB, (uint32_t)((c0 + c) * SBW + (SB + lj - c)), tbw[lj * (SB + 1) + c]);
           }
         }
         wave_sync();
@@ -686,7 +691,7 @@ __global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0, 
         const int c = 16 * h + q, i = c + lj;
         if (i < ln) {
           D[q] = fmaf(-vbw[i], wbw[c], fmaf(-wbw[i], vbw[c], D[q]));
-          band_st(AB, (uint32_t)((r0 + c) * SBW + lj), D[q]);
+          band_st<SCOPE>(AB, (uint32_t)((r0 + c) * SBW + lj), D[q]);
         }
       }
       // E <- E H (row layout: lane (i, h) holds columns 16 h ..)
@@ -707,7 +712,7 @@ __global__ void __launch_bounds__(BG_WAVES * 64) k_sb_bulge(SbArgs a, int mat0, 
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
           const int c = 16 * h + q;
-          if (c < ln) band_st(AB, (uint32_t)((r0 + c) * SBW + (ln - c)), E[q]);
+          if (c < ln) band_st<SCOPE>(AB, (uint32_t)((r0 + c) * SBW + (ln - c)), E[q]);
         }
       }
       if (ne < 2) break;
@@ -1081,7 +1086,8 @@ hipError_t launch_sb_reduce(const EigBatch &b, float *work, const GemmProblem *t
   // matrices 458 or 537 to 396 ms, 240 of order 1100 68 to 46).
   const int groups = std::max(1, std::min({4, (n + 1199) / 1200, 64 / nm}));
   hipLaunchKernelGGL(k_sb_bulge_clear, dim3(nm), dim3(256), 0, st, a, m0);
-  hipLaunchKernelGGL(k_sb_bulge, dim3(nm * groups), dim3(BG_WAVES * 64), 0, st, a, m0, groups);
+  if (groups > 1) hipLaunchKernelGGL(k_sb_bulge<__HIP_MEMORY_SCOPE_AGENT>, dim3(nm * groups), dim3(BG_WAVES * 64), 0, st, a, m0, groups);
+  else hipLaunchKernelGGL(k_sb_bulge<__HIP_MEMORY_SCOPE_WORKGROUP>, dim3(nm), dim3(BG_WAVES * 64), 0, st, a, m0, 1);
   hipLaunchKernelGGL(k_sb_bulge_finish, dim3(nm), dim3(256), 0, st, a, m0);
   return hipGetLastError();
 }
