@@ -1033,40 +1033,49 @@ __global__ void __launch_bounds__(256) k_attend_combine(AttnArgs a) {
     if (lane == 0) Ls[r] = L;
   }
   __syncthreads();
-  // a_r[i] = sum_c w_c a_c[i], b_r[f] = sum_c w_c b_c[f], chunks in order
+  // a_r[i] = sum_c w_c a_c[i], b_r[f] = sum_c w_c b_c[f], chunks in order: U columns of 16 / U
+  // chunks in flight per thread, no more columns than the call has (three of four loads of 160
+  // columns repeated the last one: 1 item of 4 x 2 heads over 32768 tokens 135 -> 93 us in all)
   const int nc = rep * ncol;
-  for (int q0 = tid; q0 < nc; q0 += 4 * 256) {
-    const JOLT_GLOBAL float *pc[4];
-    const float *wc[4];
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    int rr[4], ii[4];
+  auto sum_columns = [&](auto u_) {
+    constexpr int U = decltype(u_)::value, K = 16 / U;
+    for (int q0 = tid; q0 < nc; q0 += U * 256) {
+      const JOLT_GLOBAL float *pc[U];
+      const float *wc[U];
+      float acc[U];
+      int rr[U], ii[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int q = min(q0 + 256 * u, nc - 1);
-      rr[u] = q / ncol; ii[u] = q - rr[u] * ncol;
-      pc[u] = gptr(part) + (int64_t)rr[u] * stride + 2 + (ii[u] < vb.rT ? ii[u] : a.rv_max + (ii[u] - vb.rT));
-      wc[u] = cw + rr[u] * a.chunks;
+      for (int u = 0; u < U; ++u) {
+        const int q = min(q0 + 256 * u, nc - 1);
+        acc[u] = 0.f;
+        rr[u] = q / ncol; ii[u] = q - rr[u] * ncol;
+        pc[u] = gptr(part) + (int64_t)rr[u] * stride + 2 + (ii[u] < vb.rT ? ii[u] : a.rv_max + (ii[u] - vb.rT));
+        wc[u] = cw + rr[u] * a.chunks;
+      }
+      for (int c0 = 0; c0 < a.chunks; c0 += K) {
+        float v[K][U];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+          for (int u = 0; u < U; ++u) v[k][u] = c0 + k < a.chunks ? pc[u][(int64_t)(c0 + k) * cstride] : 0.f;
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+          if (c0 + k < a.chunks) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc[u] = fmaf(wc[u][c0 + k], v[k][u], acc[u]);
+          }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (q0 + 256 * u >= nc) break;
+        if (ii[u] < vb.rT) av[rr[u] * lda + ii[u]] = acc[u];
+        else bv[rr[u]][ii[u] - vb.rT] = acc[u];
+      }
     }
-    for (int c0 = 0; c0 < a.chunks; c0 += 4) {
-      float v[4][4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[k][u] = c0 + k < a.chunks ? pc[u][(int64_t)(c0 + k) * cstride] : 0.f;
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (c0 + k < a.chunks) {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) acc[u] = fmaf(wc[u][c0 + k], v[k][u], acc[u]);
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (q0 + 256 * u >= nc) break;
-      if (ii[u] < vb.rT) av[rr[u] * lda + ii[u]] = acc[u];
-      else bv[rr[u]][ii[u] - vb.rT] = acc[u];
-    }
-  }
+  };
+  if (nc <= 256) sum_columns(std::integral_constant<int, 1>{});
+  else if (nc <= 512) sum_columns(std::integral_constant<int, 2>{});
+  else sum_columns(std::integral_constant<int, 4>{});
   __syncthreads();
   // inverse rotation of the residual sums (in place), while the factor products follow
   if (vb.bits && tid < RM * LW) {
@@ -1137,6 +1146,8 @@ hipError_t launch_ends(const AttnArgs &a, const AttnItemTable &tab, bool prep, h
   return hipGetLastError();
 }
 
+constexpr int COMBINE_WGS = 256;
+
 template <int D>
 hipError_t launch_attend_d(const AttnArgs &a, const AttnItemTable &tab, hipStream_t st) {
   const int rep = a.n_q / a.heads;
@@ -1155,10 +1166,13 @@ hipError_t launch_attend_d(const AttnArgs &a, const AttnItemTable &tab, hipStrea
     e = hipGetLastError();
   }
   if (e != hipSuccess) return e;
-  // the heads of a key-value head share one combine workgroup while their chunk weights fit
-  // 16 KB of LDS
-  if (rep > 4 && a.chunks <= 512) return launch_ends<D, 8>(a, tab, false, st);
-  if (rep > 1 && a.chunks <= 1024) return launch_ends<D, 4>(a, tab, false, st);
+  // The heads of a key-value head share one combine workgroup (its factors are read once) while the
+  // chunk weights fit 16 KB of LDS and the call still fills the chip.  A workgroup walks all chunks of
+  // its heads, so few items get one workgroup per query head: 1 item of 8 x 8 heads, shared to not,
+  // in all: 300 tokens 45 to 35 us, 8192 99 to 65, 32768 at ranks (300, 260) 794 to 523.
+  const int64_t wgs = (int64_t)a.n_items * a.heads;
+  if (rep > 4 && a.chunks <= 512 && wgs >= COMBINE_WGS) return launch_ends<D, 8>(a, tab, false, st);
+  if (rep > 1 && a.chunks <= 1024 && wgs * ((rep + 3) / 4) >= COMBINE_WGS) return launch_ends<D, 4>(a, tab, false, st);
   return launch_ends<D, 1>(a, tab, false, st);
 }
 

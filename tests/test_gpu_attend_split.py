@@ -48,3 +48,21 @@ def test_chunk_pass_edges(case):
         want = oat.attend(K, V, layer, H, Q[i], 1.0 / np.sqrt(d))
         for j in range(rep * H):
             assert np.abs(got[i, j] - want[j]).max() <= TOL * np.linalg.norm(want[j]), (i, j)
+
+
+# calls of enough workgroups that a key-value head's query heads share a combine workgroup (four, five
+# of eight, eight of them)
+@pytest.mark.parametrize("d, rep, T, v_rT", [(128, 4, 70, 16), (64, 5, 70, 24), (64, 8, 200, 40)])
+def test_many_items(d, rep, T, v_rT):
+    H, n = 8, 32
+    rng = np.random.default_rng(12)
+    K, V = _cell(rng, H, T, d, 1.5), _cell(rng, H, T, d, 0.7) + 0.2 * rng.standard_normal((H, T, d))
+    kb, vb = _oracle_blob(K, H, 24, 16, 4, 32, 5), _oracle_blob(V, H, v_rT, 24, 4, 32, 6)
+    Q = rng.standard_normal((n, rep * H, d))
+    got = _run([kb] * n, [vb] * n, [0] * n, Q, d)
+    K, V = opl.decode_blob(kb), opl.decode_blob(vb)
+    Q = Q.astype(np.float32).astype(np.float64)
+    for i in range(0, n, 5):
+        want = oat.attend(K, V, 0, H, Q[i], 1.0 / np.sqrt(d))
+        for j in range(rep * H):
+            assert np.abs(got[i, j] - want[j]).max() <= TOL * np.linalg.norm(want[j]), (i, j)
