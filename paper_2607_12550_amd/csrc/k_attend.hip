@@ -1181,10 +1181,14 @@ hipError_t launch_attend_d(const AttnArgs &a, const AttnItemTable &tab, hipStrea
 // How a call is split: the matrix-core chunk pass takes fp16 factors with ranks in multiples of
 // 8 (aligned 16-byte factor rows), groups of 32 features or more (one scale per 32-wide step)
 // and value ranks up to 512 with key ranks up to 1024 (its LDS); the rest runs on the vector
-// kernel.  A workgroup walks several 64-token tiles (fewer partials to write and merge) as long
+// kernel.  Past value ranks of 256 its registers leave one workgroup to a CU, which pays only where
+// four or more query heads share it and it walks several tiles: at value rank 264, matrix cores to
+// vector pass, 8 heads of 4096 tokens: 32 items x 8 queries 572 to 1014 us, x 4 600 to 635, x 2 582
+// to 533, x 1 574 to 428; 8 items x 8 226 to 276, x 4 218 to 179; 4 items x 8 173 to 160.  A workgroup walks several 64-token tiles (fewer partials to write and merge) as long
 // as about 2048 workgroups remain, four rounds of the 512 that fit the chip.
-bool attend_use_mfma(const AttnItem *items, int n, int d, int group, int rep, int rk, int rv) {
+bool attend_use_mfma(const AttnItem *items, int n, int heads, int T, int d, int group, int rep, int rk, int rv) {
   if (group % 32 || d % group || rv > 512) return false;
+  if (rv > 256 && (rep < 4 || (int64_t)((T + 63) / 64) * heads * n * rep < 32768)) return false;
   for (int i = 0; i < n; ++i)
     for (const AttnBlob *b : {&items[i].k, &items[i].v})
       if (!b->f16 || b->rT % 8 || (b->bits != 0 && b->bits != 2 && b->bits != 4 && b->bits != 8)) return false;

@@ -222,7 +222,7 @@ constexpr int ATTN_CHUNK = 64;      // tokens per workgroup of the vector chunk 
 constexpr int ATTN_QMAX = 64;       // query heads per item
 constexpr int ATTN_REP_MAX = 8;     // query heads per key-value head
 constexpr int ATTN_RT_MAX = 1024;   // largest value rank the combine kernel stages in LDS
-bool attend_use_mfma(const AttnItem *items, int n, int d, int group, int rep, int rk, int rv);
+bool attend_use_mfma(const AttnItem *items, int n, int heads, int T, int d, int group, int rep, int rk, int rv);
 int attend_chunk_tokens(int n_items, int heads, int T);
 hipError_t launch_attend(const AttnArgs &a, const AttnItemTable &tab, int d, hipStream_t st);
 // fixed per-device scratch of the allocation-free attention entry point

@@ -1560,7 +1560,7 @@ int attend_impl(jolt_ctx *ctx, int n_items, const void *const *k_blobs, const si
   a.items = items; a.Q = Q; a.O = O; a.gk = gk; a.qr = qr; a.part = part;
   a.n_items = n_items; a.n_q = n_q; a.heads = H; a.T = T; a.group = kb[0].group;
   a.rk_max = std::max(rk, 1); a.rv_max = rv;
-  a.mfma = attend_use_mfma(hi.data(), n_items, d, a.group, n_q / H, a.rk_max, rv) ? 1 : 0;
+  a.mfma = attend_use_mfma(hi.data(), n_items, H, T, d, a.group, n_q / H, a.rk_max, rv) ? 1 : 0;
   a.chunk_tokens = a.mfma ? attend_chunk_tokens(n_items, H, T) : ATTN_CHUNK;
   a.chunks = (T + a.chunk_tokens - 1) / a.chunk_tokens;
   a.per_xcd = (int)(((int64_t)n_items * a.chunks * H + 7) / 8);

@@ -51,8 +51,8 @@ def test_chunk_pass_edges(case):
 
 
 # calls of enough workgroups that a key-value head's query heads share a combine workgroup (four, five
-# of eight, eight of them)
-@pytest.mark.parametrize("d, rep, T, v_rT", [(128, 4, 70, 16), (64, 5, 70, 24), (64, 8, 200, 40)])
+# of eight, eight of them), the last with value ranks past 256 on the matrix cores
+@pytest.mark.parametrize("d, rep, T, v_rT", [(128, 4, 70, 16), (64, 5, 70, 24), (64, 8, 1024, 264)])
 def test_many_items(d, rep, T, v_rT):
     H, n = 8, 32
     rng = np.random.default_rng(12)
