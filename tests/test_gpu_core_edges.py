@@ -44,3 +44,17 @@ def test_codes_and_decoded_rows(case):
     out = decompress(blobs, desc, "bf16")[0]
     rms = np.sqrt((want ** 2).mean())
     assert (np.abs(out - want) <= 2.0 ** -8 * np.abs(want) + 1e-5 * rms).all()
+
+
+@pytest.mark.parametrize("d, T, bits", [(64, 65, 8), (128, 128, 4)])
+def test_short_slices_in_one_call_or_alone(d, T, bits):
+    """512 slices of at most 128 tokens are decoded by the staged kernel, those of one cell alone by
+    the resident one: the same bits."""
+    n, m = 8, 64
+    rng = np.random.default_rng(d)
+    cells = [rng.standard_normal((m, T, 8)) @ rng.standard_normal((8, d)) + 0.3 * rng.standard_normal((m, T, d)) for _ in range(n)]
+    xs, ex, desc = device_cells(cells, "bf16")
+    blobs, _ = compress(xs, desc, [J.Params(24, 16, bits, 32, J.JOLT_FACTOR_F16, 0, i) for i in range(n)])
+    both = decompress(blobs, desc, "bf16")
+    for i in (0, n - 1):
+        assert np.array_equal(both[i], decompress(blobs[i:i + 1], desc, "bf16")[0])
