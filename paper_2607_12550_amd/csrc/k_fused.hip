@@ -983,8 +983,9 @@ __global__ void __launch_bounds__(NT, sizeof(TIO) == 2 ? 2 : 1) k_core(FusedArgs
 }
 
 // ------------------------------------------------------- core path, factors resident in LDS
-// The same arithmetic as k_core, in the same order (the outputs are equal bit for bit), for bf16
-// caches of d >= 64 whose U^_d and G^_s^T fit the LDS together.  k_core waited most of its time:
+// The same arithmetic as k_core, in the same order (without RoPE the outputs are equal bit for bit;
+// its angles are formed otherwise, below), for bf16 caches of d >= 64 whose U^_d and G^_s^T fit the
+// LDS together.  k_core waited most of its time:
 // one tile per workgroup, every operand chunk and every row staged through LDS between barriers.
 // Here a workgroup of eight waves keeps U^_d and G^_s^T of one slice in LDS and each wave walks
 // 32-token tiles of that slice on its own, with no barrier in the loop:

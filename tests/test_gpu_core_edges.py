@@ -11,10 +11,11 @@ import pytest
 import torch
 
 import paper_2607_12550_amd as J
-from gpu_util import blob_bytes, compress, ctx, decompress, device_cells
+from gpu_util import blob_bytes, compress, ctx, decompress, device_cells, note, workspace
 from oracle import pipeline as opl
 from oracle.philox import rotation_signs
 from oracle.residual import quantize, rotate
+from oracle.rope import rope
 
 pytestmark = pytest.mark.gpu
 
@@ -58,3 +59,21 @@ def test_short_slices_in_one_call_or_alone(d, T, bits):
     both = decompress(blobs, desc, "bf16")
     for i in (0, n - 1):
         assert np.array_equal(both[i], decompress(blobs[i:i + 1], desc, "bf16")[0])
+
+
+@pytest.mark.parametrize("d, T, offset", [(64, 33, 0), (64, 289, 100000), (128, 33, 1000000), (128, 289, 123457)])
+def test_rope_at_large_positions(d, T, offset):
+    """Rows decoded with RoPE against the oracle's rotation of its decode, ragged lengths and large
+    positions (the angle is reduced in fp64: its error stays below 1e-9 at 1e6)."""
+    rng = np.random.default_rng(T + d)
+    X = rng.standard_normal((4, T, 8)) @ rng.standard_normal((8, d)) + 0.3 * rng.standard_normal((4, T, d))
+    xs, ex, desc = device_cells([X], "bf16")
+    blobs, _ = compress(xs, desc, [J.Params(16, 16, 4, 32, J.JOLT_FACTOR_F16, 0, 5)])
+    want = rope(opl.decode_blob(blob_bytes(blobs[0])), 1e6, np.arange(T) + float(offset))
+    out = torch.empty((4, T, d), dtype=torch.bfloat16, device="cuda")
+    note("jolt_decompress_rope d", d, "T", T, "offset", offset)
+    J.jolt_decompress(ctx(), blobs, desc, [out], workspace(desc, 1), rope=(1e6, offset))
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy().astype(np.float64)
+    rms = np.sqrt((want ** 2).mean())
+    assert (np.abs(got - want) <= 2.0 ** -8 * np.abs(want) + 1e-5 * rms).all()
