@@ -808,19 +808,25 @@ bool gemm16_prepare(GemmProblem *probs, int n, int &ta, int &tb, bool &ak, bool 
   for (int i = 1; i < n; ++i)
     if ((probs[i].lower_only != 0) != (probs[0].lower_only != 0)) return false;
   int maxM = 0, minK = 1 << 30;
+  int64_t tiles256 = 0;      // workgroups with 256 x 128 tiles
   bool lower = false;
   for (int i = 0; i < n; ++i) {
     GemmProblem &p = probs[i];
     if (swap) { std::swap(p.A, p.B); std::swap(p.M, p.N); p.c_trans = 1; }
     maxM = std::max(maxM, p.M);
     minK = std::min(minK, p.K);
+    tiles256 += (int64_t)((p.M + 255) / 256) * ((p.N + 127) / 128);
     lower = lower || p.lower_only;
   }
   if (swap) { std::swap(ta, tb); std::swap(ak, bk); }
   // 256-row tiles for products of a bf16 operand over long M and a split one: the K loop is bound
   // by LDS bandwidth, and a wave's 128 x 64 block reads eight fragments per 16 products where its
   // 64 x 64 block reads six per eight (X^T Q and Q^T X of 16 cells at T = 32768: 8.9 ms with
-  // 128 rows, 7.6 with 256; X Q': 7.0); 256 x 256 tiles for large lower-triangle bf16 tables with
+  // 128 rows, 7.6 with 256; X Q': 7.0).  An m-contiguous bf16 operand (transposed on its way to
+  // LDS) keeps 128 rows while 256 would leave more than a quarter of the CUs without a workgroup:
+  // range finder and spectrum of 2 cells of 4096 columns, 96 workgroups with 256 rows, T = 8192: 8.75
+  // ms with 128 rows, 8.95 with 256; 160 (T = 131072) 40.4 and 40.7; 192 (4 cells, T = 10000) 10.95 and
+  // 10.84; 320 21.5 and 21.3.  256 x 256 tiles for large lower-triangle bf16 tables with
   // a long K (the token Gram of wide cells: each K step moves 512 operand rows for 256 x 256
   // outputs, and each wave's 128 x 128 block reads 8 fragments per 16 MFMAs, where the
   // 128 x 128 tiles read 4 per 4 and leave the K loop bound by LDS bandwidth); 128 otherwise
@@ -829,7 +835,7 @@ bool gemm16_prepare(GemmProblem *probs, int n, int &ta, int &tb, bool &ak, bool 
   bool k64 = true;
   for (int i = 0; i < n; ++i) k64 = k64 && probs[i].K % BK == 0;
   if (lower && bf_both && k64 && maxM >= 2048 && minK >= 16384) bm = GEMM16_SQUARE256;
-  else bm = (tb == GT_F32 && ta == GT_BF16 && maxM >= 2048 && !lower) ? 256 : 128;
+  else bm = (tb == GT_F32 && ta == GT_BF16 && maxM >= 2048 && !lower && (ak || tiles256 >= 192)) ? 256 : 128;
   return true;
 }
 

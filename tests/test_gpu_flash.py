@@ -187,3 +187,19 @@ def test_flash_rank_deficient_cell_stays_finite():
     blobs, _ = compress(xs, desc, [J.Params(6, 6, 0, 64, J.JOLT_FACTOR_F32, 0, 4)], o, ws=ws)
     Xh = decompress(blobs, desc, "f32")[0]
     assert np.linalg.norm(Xh - ex[0]) <= 1e-5 * np.linalg.norm(ex[0])
+
+
+def test_spectrum_in_small_and_large_batches():
+    """The products with the sketch take 128-row tiles in a call of few cells and 256-row tiles in
+    one of many (2048 x 160; 32 and 256 workgroups): the same cells give the same spectra to fp32
+    sums in another order (1e-5 of lambda_1)."""
+    T, H, n = 900, 16, 16
+    base = [kv_cell(T, H, 128, seed=s) for s in (0, 1)]
+    xs, ex, desc = device_cells([base[i % 2] * (1.0 + i / 16.0) for i in range(n)], "bf16")
+    o, seeds = flash_opts(150), list(range(n))
+    note("FlashJoLT spectrum of", n, "cells, then of two of them")
+    lam = np.array(J.jolt_spectrum(ctx(), desc, xs, seeds, o, workspace(desc, n, o))[1])
+    pick = [3, n - 2]
+    few = np.array(J.jolt_spectrum(ctx(), desc, [xs[i] for i in pick], pick, o, workspace(desc, 2, o))[1])
+    assert np.abs(lam[pick] - few).max(axis=1).max() <= 1e-5 * few[:, 0].min()
+    assert (lam[:, 0] > 0).all()
