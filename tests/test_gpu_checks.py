@@ -137,17 +137,19 @@ def test_tiny_core_takes_the_exponent_floor():
     assert np.linalg.norm(Xh - want) <= 1e-5 * np.linalg.norm(want)
 
 
-def test_tridiagonalisation_lanes_do_not_change_results():
+@pytest.mark.parametrize("two_stage", [0, 1])
+def test_tridiagonalisation_lanes_do_not_change_results(two_stage):
     """The exact spectrum of a batch of cells is the same bit for bit whether the blocked
-    tridiagonalisation runs its matrices as one group on one stream or as several groups on
-    up to four streams (JOLT_DBG_TRD_LANES; three cells, so 3 and 4 both give three groups);
-    the setting rejects values outside 1..4."""
-    cells = [keys(T=1024, H=8, seed=s) for s in range(3)]      # T above the one-workgroup size
+    tridiagonalisation (one or two stages) runs its matrices as one group on one stream or as
+    several groups on up to four streams (JOLT_DBG_TRD_LANES; three cells, so 3 and 4 both give
+    three groups); the setting rejects values outside 1..4."""
+    cells = [keys(T=1100, H=8, seed=s) for s in range(3)]      # past the orders kept in registers
     xs, ex, desc = device_cells(cells, "bf16")
     ws = workspace(desc, 3)
     out = []
     c2 = J.jolt_create(0)
     try:
+        J.jolt_debug_set(c2, J.JOLT_DBG_TRD_TWO_STAGE, two_stage)
         for lanes in (1, 2, 3, 4):
             J.jolt_debug_set(c2, J.JOLT_DBG_TRD_LANES, lanes)
             note("exact spectrum, tridiagonalisation lanes", lanes)
@@ -165,7 +167,7 @@ def test_tridiagonalisation_lanes_do_not_change_results():
 
 
 def test_two_stage_and_one_stage_reductions_agree():
-    """JOLT_DBG_TRD_TWO_STAGE: for T > 768 (here T = 1100, a ragged last panel) the exact
+    """JOLT_DBG_TRD_TWO_STAGE: past the orders kept in registers (here T = 1100, a ragged last panel) the exact
     token spectrum from the two-stage reduction (band of half-bandwidth 32 by panel QR and
     rank-64 updates, then bulge chasing) and from the one-stage blocked reduction agree within
     1e-5 of lambda_1 on fp32 cells, and the token factors at a gapped rank span the same

@@ -197,8 +197,8 @@ def reduction(request):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_blocked_tridiagonalisation_spectrum_and_subspace(dtype, reduction):
-    """T = 1024 > 768 takes the blocked multi-workgroup tridiagonalisation (one or two
-    stages)."""
+    """T = 1024 with the blocked multi-workgroup tridiagonalisation asked for by name (one or two
+    stages; the automatic choice keeps two matrices of that order in registers)."""
     X = keys_cell(T=1024, H=4)
     xs, ex, desc = device_cells([X, keys_cell(T=1024, H=4, seed=5)], dtype)
     ws = workspace(desc, 2)
