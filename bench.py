@@ -467,10 +467,11 @@ def method_comparison(K, V, gl, ratio, args, exact_compress_ms):
 
 def trd_stages_used(args, cells_per_call, T):
     """Reduction of the exact token Grams to tridiagonal form in this run: the forced one, or
-    the library's automatic choice (two stages once a call's matrices times T reach
-    32 * 4096; T up to 768 is reduced in one workgroup per matrix)."""
-    if T <= 768:
-        return "one-workgroup"
+    the library's automatic choice (in registers, or by one workgroup per matrix, up to T = 768,
+    up to 1024 for at most 8 matrices a call; else two stages once a call's matrices times T
+    reach 32 * 4096)."""
+    if T <= 768 or (T <= 1024 and cells_per_call <= 8 and args.trd_stages not in (1, 2)):
+        return "registers"
     if args.trd_stages in (1, 2):
         return "two-stage" if args.trd_stages == 2 else "one-stage"
     return "two-stage" if cells_per_call * T >= 32 * 4096 else "one-stage"

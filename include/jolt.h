@@ -298,7 +298,7 @@ int jolt_eps2_calibrate(jolt_ctx *ctx, int group, int d, uint64_t seed, int n_sa
  * jolt_allocate takes tau = (E - their sum) / E from these rows (jolt_cell_spectrum.mu).
  * Y is formed once at r_T = n_r * step; F_Y(k step) is the running sum over k of the
  * Grams of its row blocks k (fp32 per block, fp64 running sums, fp32 matrices), then
- * diagonalised by the one-workgroup tridiagonalisation and fp64 bisection.
+ * diagonalised by the tridiagonalisation of small matrices and fp64 bisection.
  *   X, seeds, opts, stream: as jolt_spectrum.  opts->reuse = 1 takes the token spectrum a
  *         jolt_spectrum or jolt_compress call left in this same workspace for these cells
  *         (JOLT_E_STATE if there is none); 0 computes it (and records it, as jolt_spectrum).
@@ -325,7 +325,7 @@ int jolt_truncated_spectra(jolt_ctx *ctx, const jolt_cell_desc *desc, int n_cell
  * and clipped at 0, of the slice Gram S[s][s'] = sum_{t,f} X[s][t][f] X[s'][t][f] (the
  * squared singular values of the slice unfolding; for one layer, the head mode).  The
  * Gram is accumulated per token in fp32 and across tokens in fp64, reduced over token
- * chunks in a fixed order, and diagonalised by the one-workgroup tridiagonalisation and
+ * chunks in a fixed order, and diagonalised by the tridiagonalisation of small matrices and
  * fp64 bisection.  Cells, strides and X as for jolt_spectrum; m <= 768
  * (JOLT_E_UNSUPPORTED otherwise).  lam_s: host, n_cells x m doubles.  ws: device,
  * 256-byte aligned, at least jolt_slice_spectrum_workspace_size bytes, owned by the
@@ -403,11 +403,12 @@ int jolt_debug_export(jolt_ctx *ctx, int what, int cell, void *dst, size_t dst_b
  * JOLT_DBG_TRD_LANES sets how many streams the blocked tridiagonalisation of the exact token
  * spectrum spreads its groups of matrices over (default 4, range 1..4; results do not
  * depend on it): 1 keeps every launch on the call's stream, for counter collection.
- * JOLT_DBG_TRD_TWO_STAGE selects the reduction of those large matrices to tridiagonal form:
+ * JOLT_DBG_TRD_TWO_STAGE selects the reduction of matrices of order above 768 to tridiagonal form:
  * 1 the two-stage reduction (dense to a band of half-bandwidth 32 by panel QR and
  * matrix-core updates, then bulge chasing), 0 the one-stage blocked Householder reduction,
- * -1 (default) two stages when the call's matrices times their order reach 32 * 4096, one
- * otherwise; both give the same spectrum and projectors to rounding, and a compress that
+ * -1 (default) in registers up to order 1024 while the call's matrices fit the chip at once (8 of
+ * them), else two stages when the call's matrices times their order reach 32 * 4096, one
+ * otherwise; all give the same spectrum and projectors to rounding, and a compress that
  * reuses a recorded spectrum back-transforms with the reduction that made it.
  * JOLT_DBG_BULGE_SPIN bounds each wait between wavefronts of a tridiagonalisation: the two-stage
  * reduction's bulge chase and, for orders 257..1024, the exchange between the workgroups that
@@ -430,12 +431,12 @@ int jolt_debug_set(jolt_ctx *ctx, int what, int64_t value);
 enum {
   JOLT_STAGE_FEATURE_GRAM = 0, /* E and F = sum_s X_s^T X_s (and F_Y during ST-HOSVD) */
   JOLT_STAGE_TOKEN_GRAM,       /* C = X_(2) X_(2)^T */
-  JOLT_STAGE_TRIDIAG_LARGE,    /* blocked tridiagonalisation of token Grams with T > 768 (mat-vec
-                                  tiles, per-column kernels and rank-2k updates, replayed as one
-                                  graph and timed as a whole) */
+  JOLT_STAGE_TRIDIAG_LARGE,    /* blocked tridiagonalisation of large token Grams (one or two
+                                  stages, replayed as graphs and timed as a whole) */
   JOLT_STAGE_RESERVED_3,       /* not recorded */
   JOLT_STAGE_RESERVED_4,       /* not recorded */
-  JOLT_STAGE_TRIDIAG_SMALL,    /* one-workgroup tridiagonalisation (small n) */
+  JOLT_STAGE_TRIDIAG_SMALL,    /* tridiagonalisation in registers or by one workgroup per matrix:
+                                  orders up to 768, few matrices up to 1024 */
   JOLT_STAGE_EIGVALS,          /* fp64 bisection */
   JOLT_STAGE_EIGVECS,          /* fp64 inverse iteration + cluster re-orthogonalisation */
   JOLT_STAGE_BACKTRANSFORM,    /* U = Q Z */

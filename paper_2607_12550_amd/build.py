@@ -22,7 +22,7 @@ DEVICE_SOURCES = ["k_residual.hip", "k_gemm.hip", "k_gemm16.hip", "k_gram.hip", 
 HOST_SOURCES = ["api.cpp", "pipeline.cpp", "diag.cpp"]
 STRICT_FP_SOURCES = ["alloc.cpp"]
 
-COMMON = ["-std=c++17", "-O3", "-fPIC", "--offload-arch=gfx950", "-Wall", "-Wno-unused-function",
+COMMON = ["-std=c++17", "-O3", "-fPIC", "--offload-arch=gfx950", "-Wall",
           "-Wno-unused-variable", "-Wno-unused-but-set-variable"]
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

@@ -7,13 +7,16 @@
 //   value side: sum_t p_t X^_s[t] = ((sum_t p_t U_T[t]) 2^e_s G_s) U_d^T
 //                                   + signs . H (sum_t p_t r'_s[t]) / sqrt(d)
 //
-// Three kernels: k_attend_prep forms g and q' per (item, query head); k_attend_chunk runs
-// over 64-token chunks of one key-value head of one item (scores, a chunk-local softmax, and
+// Three kernels a call: k_attend_prep forms g and q' of the query heads of one key-value head of
+// one item; a chunk pass runs over token chunks of one such key-value head (scores, softmax, and
 // the value-side sums of U_T rows and dequantised codes, weighted by the unnormalised
-// probabilities, for all query heads of that key-value head at once); k_attend_combine
-// merges the chunks with the usual max / rescale rule in a fixed order and applies the
-// value factors and the inverse rotation once per query head.  Per token a query head
-// reads r_T factor values and d codes instead of d decoded values plus the decompression.
+// probabilities, for all its query heads at once); k_attend_combine merges the chunks with the
+// usual max / rescale rule in a fixed order and applies the value factors and the inverse
+// rotation.  The chunk pass is k_attend_mfma, on the matrix cores and over several 64-token tiles
+// per workgroup, for fp16 factors with ranks in multiples of 8 and quantiser groups of 32 and more,
+// the ordinary compressed cache; k_attend_chunk, vector code over one 64-token tile, for the rest
+// (attend_use_mfma).  Per token a query head reads r_T factor values and d codes instead of d
+// decoded values plus the decompression.
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -108,21 +111,6 @@ JOLT_DEV void stage_lds(float *dst, int n, F src) {
     }
   }
 }
-
-// a factor matrix of n consecutive values staged as fp32 (the storage type chosen once)
-template <int NT = 256>
-JOLT_DEV void stage_factor(float *dst, const void *p, int64_t off, int n, int f16) {
-  if (f16) {
-    const JOLT_GLOBAL _Float16 *h = gptr(reinterpret_cast<const _Float16 *>(p)) + off;
-    stage_lds<NT>(dst, n, [&](int q) { return (float)h[q]; });
-  } else {
-    const JOLT_GLOBAL float *x = gptr(reinterpret_cast<const float *>(p)) + off;
-    stage_lds<NT>(dst, n, [&](int q) { return x[q]; });
-  }
-}
-
-// Sylvester Hadamard entry (-1)^popcount(i & j)
-JOLT_DEV float hsign(int i, int j) { return (__popc((unsigned)(i & j)) & 1) ? -1.f : 1.f; }
 
 // eight consecutive factor values of a row (16-byte loads when the row start allows)
 JOLT_DEV void factor8(const void *p, int64_t i, int f16, bool vec, float (&v)[8]) {

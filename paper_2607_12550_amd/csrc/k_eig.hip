@@ -30,19 +30,6 @@ JOLT_DEV double block_sum(double v, double *red) {
   return s;
 }
 
-JOLT_DEV int sturm_count(const double *d, const double *e, int n, double x, double pivmin) {
-  double q = d[0] - x;
-  if (fabs(q) <= pivmin) q = -pivmin;
-  int cnt = q < 0.0;
-  for (int j = 1; j < n; ++j) {
-    const double ej = e[j - 1];
-    q = d[j] - x - ej * ej / q;
-    if (fabs(q) <= pivmin) q = -pivmin;
-    cnt += q < 0.0;
-  }
-  return cnt;
-}
-
 JOLT_DEV void gershgorin(const double *d, const double *e, int n, double &gl, double &gu,
                          double &pivmin) {
   gl = DBL_MAX; gu = -DBL_MAX;

@@ -27,7 +27,7 @@
 //
 // Which of this and the one-stage reduction runs is the caller's choice (by batch size:
 // the bulge chase is a chain of about n^2 / 64 dependent steps per matrix, hidden only when
-// enough matrices run side by side).
+// enough matrices run side by side, and one stage is the more accurate).
 #include <algorithm>
 
 #include "common.h"

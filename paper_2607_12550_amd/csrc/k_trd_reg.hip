@@ -36,8 +36,9 @@
 // 31 waiting workgroups give their places back.  (With (matrix, part) from the block index two
 // launches could hold one XCD each with workgroups that waited for the other's; drawing them costs
 // 0.2 of 6.9 ms at n = 1001, 0.2 of 4.6 ms for 16 matrices of order 700, nothing up to 576: the
-// parts of a matrix are then spread less evenly over the XCDs.)  A second bound (spin_max) ends the exchange's own
-// waits; a workgroup that gives up there marks its matrix in b.gave_up, which the caller reports.
+// parts of a matrix are then spread less evenly over the XCDs.)  A second bound (spin_max) ends the
+// exchange's own waits; a workgroup that gives up there marks its matrix in b.gave_up, which the
+// caller reports.
 // Whole spectrum of 4 cells, one workgroup per matrix with blocked updates -> this: T = 256 4.1 ->
 // 2.5 ms, 522 10.7 -> 5.0 ms, 700 18.1 -> 6.9 ms; against the one-stage reduction of larger
 // matrices T = 1001 21.1 -> 10.0 ms.  At n = 1300 the wave's registers spill and it loses (36 ms to

@@ -254,10 +254,12 @@ int eig_values(Run &R, EigWs &e) {
     // Two stages (band of half-bandwidth sb_band(), then bulge chasing) move the trailing
     // matrix once per panel instead of once per column, but their bulge chase is a chain of
     // about n^2 / 64 dependent steps per matrix; the one-stage reduction costs about n^3 / 6
-    // floats of trailing-matrix reads per matrix.  With the batch's matrices run side by side
-    // the chain is hidden once the batch holds n_mat * n >= 32 * 4096 (measured crossover at
-    // n = 4096: 16 matrices favour one stage, 64 two).  The eigenvector back-transform
-    // follows the choice.
+    // floats of trailing-matrix reads per matrix.  Batches of n_mat * n >= 32 * 4096 take two
+    // stages.  The time alone would put the line lower (spectrum at n = 4096, one and two stages:
+    // 8 matrices 124 and 155 ms, 16 191 and 163, 30 344 and 186), but the two-stage eigenvalues are
+    // five times further from 64-bit arithmetic (1.2e-6 against 2.3e-7 of the largest), so
+    // smaller batches keep the more accurate reduction.  The eigenvector back-transform follows the
+    // choice.
     const bool two = c->trd_two_stage == 1 ||
                      (c->trd_two_stage < 0 && (int64_t)e.b.n_mat * e.b.n >= kTwoStageMinWork);
     e.b.refl_off = two ? sb_band() : 1;
