@@ -50,9 +50,8 @@
 
 namespace {
 
-constexpr int WORD_ROWS = 16;            // rows of A whose upper part holds the exchange words
-
-// 64-bit word e of a matrix's exchange area
+// 64-bit word e of a matrix's exchange area, the upper part of its first 16 rows (8 n - 160 words or
+// more, of which 4 n + 2 are used, n > 256)
 JOLT_DEV uint64_t *word_at(float *A, int n, int e) {
   const int per = (n - 20) / 2, r = e / per, k = e - r * per;
   const int64_t o = (int64_t)r * n + 17;                  // columns > r for every r < 16
