@@ -415,7 +415,7 @@ int jolt_debug_export(jolt_ctx *ctx, int what, int cell, void *dst, size_t dst_b
  * hold a matrix (default 2^24 polls, range 0..2^24; 0 makes the first wait give up): a reduction
  * that gives up ends normally and the call reports JOLT_E_NOCONV, which lets that path be exercised.
  * JOLT_DBG_TRD_GATHER bounds the polls for all workgroups of such a matrix to be running at once
- * (default 2^16, range 0..2^24; 0 waits for none): past it one workgroup reduces the matrix, with
+ * (default 2^20, about a second, range 0..2^24; 0 waits for none): past it one workgroup reduces it, with
  * the same accuracy.  So calls of several contexts, streams or processes may reduce side by side;
  * at worst they slow each other down.
  * Errors: JOLT_E_INVAL. */

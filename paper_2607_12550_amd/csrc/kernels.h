@@ -251,7 +251,7 @@ inline __host__ __device__ int refl_off(const EigBatch &b) { return b.refl_off >
 // which one workgroup reduces it from memory; spin_max bounds the exchange's waits (b.gave_up, for
 // matrices of more than one workgroup)
 constexpr int TRD_REG_MAX = 1024;
-constexpr int TRD_GATHER_DEFAULT = 1 << 16;
+constexpr int TRD_GATHER_DEFAULT = 1 << 20;
 int trd_reg_workgroups(int n);       // workgroups per matrix
 hipError_t launch_trd_reg(const EigBatch &b, int gather_max, int spin_max, hipStream_t st);
 // Blocked multi-workgroup tridiagonalisation for large n (panels of nb columns).
