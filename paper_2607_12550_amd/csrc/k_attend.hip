@@ -1096,16 +1096,19 @@ __global__ void __launch_bounds__(256) k_attend_combine(AttnArgs a) {
 
 namespace {
 
-// workgroups that may need more than 64 KB of LDS in all have to declare it
-hipError_t allow_lds(const void *kernel, size_t dynamic) {
+// workgroups that may need more than 64 KB of LDS in all have to declare it: the kernel's limit,
+// the same from every call, so that calls of two threads cannot lower each other's
+hipError_t allow_lds(const void *kernel, size_t dynamic, size_t limit) {
   if (dynamic <= 20 * 1024) return hipSuccess;
-  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dynamic);
+  if (dynamic > limit) return hipErrorInvalidValue;
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)limit);
 }
+constexpr size_t MFMA_LDS_MAX = 150 * 1024, COMBINE_LDS_MAX = 112 * 1024;
 
 template <int D, int NT, int KS, int VU>
 hipError_t launch_mfma(const AttnArgs &a, hipStream_t st) {
   const AttnLds l = attn_lds(D, a.group, a.n_q / a.heads, a.rk_max, a.rv_max);
-  const hipError_t e = allow_lds(reinterpret_cast<const void *>(&k_attend_mfma<D, NT, KS, VU>), l.total);
+  const hipError_t e = allow_lds(reinterpret_cast<const void *>(&k_attend_mfma<D, NT, KS, VU>), l.total, MFMA_LDS_MAX);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_attend_mfma<D, NT, KS, VU>), dim3(a.per_xcd * 8), dim3(256), l.total, st, a);
   return hipGetLastError();
@@ -1126,7 +1129,7 @@ hipError_t launch_ends(const AttnArgs &a, const AttnItemTable &tab, bool prep, h
   } else {
     const int rep = a.n_q / a.heads;
     const size_t dyn = (size_t)RM * (a.chunks + a.rv_max) * sizeof(float);
-    const hipError_t e = allow_lds(reinterpret_cast<const void *>(&k_attend_combine<D, RM>), dyn);
+    const hipError_t e = allow_lds(reinterpret_cast<const void *>(&k_attend_combine<D, RM>), dyn, COMBINE_LDS_MAX);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_attend_combine<D, RM>), dim3(a.n_items, a.heads, (rep + RM - 1) / RM), dim3(256), dyn,
                        st, a);
@@ -1180,7 +1183,7 @@ bool attend_use_mfma(const AttnItem *items, int n, int heads, int T, int d, int 
   for (int i = 0; i < n; ++i)
     for (const AttnBlob *b : {&items[i].k, &items[i].v})
       if (!b->f16 || b->rT % 8 || (b->bits != 0 && b->bits != 2 && b->bits != 4 && b->bits != 8)) return false;
-  return attn_lds(d, group, rep, rk, rv).total <= 150 * 1024;
+  return attn_lds(d, group, rep, rk, rv).total <= (int)MFMA_LDS_MAX;
 }
 
 int attend_chunk_tokens(int n_items, int heads, int T) {

@@ -430,7 +430,8 @@ hipError_t launch_tridiag_eigvals(const EigBatch &b, hipStream_t st) {
   const void *fn = bisect ? reinterpret_cast<const void *>(&k_tri_eigvals<1>)
                           : reinterpret_cast<const void *>(&k_tri_eigvals<3>);
   if (shm > 65536) {
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+    // the limit, not this call's size: calls of two threads cannot lower each other's
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, std::max((int)shm, 128 * 1024));
     if (e != hipSuccess) return e;
   }
   if (bisect) hipLaunchKernelGGL(k_tri_eigvals<1>, grid, dim3(EV_THREADS), shm, st, b);

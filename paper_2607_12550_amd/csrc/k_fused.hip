@@ -1439,6 +1439,8 @@ hipError_t launch_core(const FusedArgs &a, int io_dtype, bool rope, hipStream_t 
   return hipGetLastError();
 }
 
+constexpr int CORE_W_LDS_MAX = 160 * 1024 - 512;      // declared the same by every call (and thread)
+
 // The resident-factor kernel's calls: bf16 caches, a code row of whole 16-byte pieces (d >= 64),
 // at most four group scales a row (one 8-byte read), factors within the LDS.  Up to 128 tokens half
 // or more of its eight waves have no tile, and decoding without RoPE the staged kernel, which covers
@@ -1449,7 +1451,7 @@ template <int D, int MODE>
 bool core_w_takes(const FusedArgs &a, int io_dtype, bool rope) {
   if (MODE == FUSED_DECODE && !rope && a.T <= 128 && (int64_t)a.n_cells * a.m >= 512) return false;
   if (D < 64 || MODE == FUSED_XTILDE || io_dtype != JOLT_BF16 || a.group * 4 < D) return false;
-  return core_w_lds(D, (a.rd_max + 31) & ~31, (a.rT_max + 15) & ~15) <= 160 * 1024 - 512;
+  return core_w_lds(D, (a.rd_max + 31) & ~31, (a.rT_max + 15) & ~15) <= CORE_W_LDS_MAX;
 }
 
 // A workgroup walks as many 256-token rounds of its slice as leave about 512 workgroups, two
@@ -1464,7 +1466,7 @@ hipError_t launch_core_w(FusedArgs a, bool rope, hipStream_t st) {
   const int lds = core_w_lds(D, (a.rd_max + 31) & ~31, (a.rT_max + 15) & ~15);
   auto go = [&](auto kernel) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, CORE_W_LDS_MAX);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(a.per_xcd * 8)), dim3(CW_NT), lds, st, a);
     return hipGetLastError();

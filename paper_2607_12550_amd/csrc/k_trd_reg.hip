@@ -582,7 +582,8 @@ hipError_t launch_sytd2(const EigBatch &b, int left, hipStream_t st) {
   const size_t shm = sytd2_lds_bytes(b.n);
   if (shm > 65536) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sytd2),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)sytd2_lds_bytes(SYTD2_THREADS));
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k_sytd2, dim3(b.n_mat), dim3(SYTD2_THREADS), shm, st, b, left);
