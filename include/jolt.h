@@ -354,7 +354,7 @@ int jolt_mode_summary(const double *lam, int n, double err_a, double err_b, doub
  * them: the key scores are U_T (2^e G_s U_d^T q) plus the dequantised codes dotted with
  * the query rotated once (H (signs . q) / sqrt(d)), and the value side sums U_T rows and
  * dequantised codes under the softmax weights before the value factors and the inverse
- * rotation are applied once per head.  fp32 arithmetic; chunks of 64 tokens are merged
+ * rotation are applied once per head.  fp32 accuracy; chunks of 64 to 4096 tokens are merged
  * with the max / rescale rule in a fixed order (deterministic).  Keys are used as stored
  * (no position rotation is applied).
  * k_hdr_host / v_hdr_host: host copies of the n_items 128-byte blob headers (validated
